@@ -317,7 +317,7 @@ typedef struct {
     int waves_m, waves_n; /* wave grid; each wave owns (bm/waves_m) x (bn/waves_n) */
     int threads;     /* work-group size */
     int trans_a, trans_b; /* operand layouts read (1 = transposed storage) */
-    int vec_a, vec_b; /* elements per global load */
+    int vec_a, vec_b; /* elements per global load (direct-to-LDS forms: per copy, at most) */
     int stages;      /* LDS buffers (2 = double buffered, 3 = two K-blocks in flight) */
     int lds_bytes;   /* LDS per work-group */
     int occupancy;   /* waves per SIMD its registers are allotted for (1 = unconstrained) */

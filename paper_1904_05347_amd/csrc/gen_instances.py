@@ -82,7 +82,8 @@ KSPLIT = [(64, 64, 16, 2, 2, 4, 1, 4, 4, 1), (64, 64, 32, 2, 2, 4, 1, 4, 4, 1), 
 DMA = [(256, 256, 16, 2, 4, 2, 2), (256, 256, 16, 2, 4, 3, 2), (256, 256, 16, 2, 4, 4, 2), (256, 256, 32, 2, 4, 2, 2),
        (128, 128, 32, 2, 4, 2, 2), (128, 128, 32, 2, 4, 3, 2), (128, 128, 32, 2, 4, 4, 2),
        (128, 128, 16, 2, 2, 3, 1), (128, 128, 16, 2, 2, 4, 1), (64, 64, 32, 2, 2, 3, 1),
-       (64, 64, 32, 2, 2, 2, 1), (64, 64, 16, 2, 2, 3, 1)]
+       (64, 64, 32, 2, 2, 2, 1), (64, 64, 16, 2, 2, 3, 1),
+       (128, 32, 32, 4, 1, 2, 1), (128, 96, 32, 4, 1, 2, 1), (128, 64, 32, 2, 2, 2, 1), (32, 64, 32, 1, 2, 3, 1)]
 
 # K-split forms of the direct-to-LDS contraction ("_kN_..._dmaS"): (BM, BN,
 # BK, WAVES_M, WAVES_N, groups, stages, OCC)
@@ -96,7 +97,21 @@ DMA_KSPLIT_CONV = [(64, 64, 32, 2, 2, 2, 3, 1), (64, 64, 32, 2, 2, 4, 2, 1), (12
 # Stream-K forms of the direct-to-LDS contraction (NN GEMM and convolution).
 DMA_STREAMK = [(128, 128, 32, 2, 4, 2, 2), (128, 128, 16, 2, 2, 3, 1), (128, 128, 32, 2, 4, 3, 2)]
 
-# TT only needs a large, a small and a scalar-load tile.
+# Forms without 16-byte alignment ("v11": vector width 1), every layout: the
+# rules' tiles of the direct-to-LDS and K-split forms.  Convolutions also in
+# "v41" (image aligned, an output channel count that is no multiple of four).
+DMA_U = [(256, 256, 32, 2, 4, 2, 2), (128, 128, 32, 2, 4, 2, 2), (64, 64, 32, 2, 2, 2, 1), (64, 64, 16, 2, 2, 3, 1),
+         (128, 32, 32, 4, 1, 2, 1), (128, 96, 32, 4, 1, 2, 1), (128, 64, 32, 2, 2, 2, 1), (32, 64, 32, 1, 2, 3, 1)]
+DMA_KSPLIT_U = [(32, 64, 32, 1, 2, 4, 3, 1), (64, 64, 32, 2, 2, 2, 3, 1), (64, 64, 32, 2, 2, 4, 2, 1)]
+CONV_DMA_U = [(128, 128, 32, 2, 4, 2, 2), (64, 64, 32, 2, 2, 2, 1), (64, 64, 16, 2, 2, 3, 1),
+              (128, 32, 32, 4, 1, 2, 1), (128, 96, 32, 4, 1, 2, 1), (128, 64, 32, 2, 2, 2, 1), (32, 64, 32, 1, 2, 3, 1)]
+CONV_DMA_KSPLIT_U = [(64, 64, 32, 2, 2, 2, 3, 1)]
+# TT: the rules' direct-to-LDS and K-split forms
+DMA_TT = [(256, 256, 32, 2, 4, 2, 2), (128, 128, 32, 2, 4, 2, 2), (64, 64, 32, 2, 2, 2, 1), (64, 64, 16, 2, 2, 3, 1),
+          (128, 32, 32, 4, 1, 2, 1), (128, 96, 32, 4, 1, 2, 1), (128, 64, 32, 2, 2, 2, 1), (32, 64, 32, 1, 2, 3, 1)]
+DMA_KSPLIT_TT = [(32, 64, 32, 1, 2, 4, 3, 1), (64, 64, 32, 2, 2, 2, 3, 1), (64, 64, 32, 2, 2, 4, 2, 1)]
+
+# TT's register-staged tiles: a large, a small and a scalar-load one.
 TT_TILES = [(128, 128, 16, 2, 2, 4, 4, 1), (64, 64, 16, 2, 2, 4, 4, 1), (64, 64, 16, 2, 2, 1, 1, 1)]
 
 CONV_TILES = [
@@ -195,18 +210,29 @@ def main():
                            % ("gemm_%dx%dx%d_w%dx%d_k%d_%s_v%d%d%s" % (bm, bn, bk, wm, wn, ks, layout, va, vb,
                                                                     "_d2" if ahead == 2 else ""),
                               bm, bn, bk, wm, wn, ks, ahead, ta, tb, va, vb, occ))
-        for t in (DMA if layout != "tt" else []):
+        for t in (DMA if layout != "tt" else DMA_TT):
             bm, bn, bk, wm, wn, st, occ = t
             entries.append("PK_GEMM_DMA(%s, %d, %d, %d, %d, %d, %d, %d, %d, %d)"
                            % ("gemm_%dx%dx%d_w%dx%d_%s_v44%s_dma%d" % (bm, bn, bk, wm, wn, layout,
                                                                      "_o%d" % occ if occ > 1 else "", st),
                               bm, bn, bk, wm, wn, st, ta, tb, occ))
-        for t in (DMA_KSPLIT if layout != "tt" else []):
+        for t in (DMA_KSPLIT if layout != "tt" else DMA_KSPLIT_TT):
             bm, bn, bk, wm, wn, ks, st, occ = t
-            if (ta and bm % 64) or (not tb and bn % 64):
-                continue  # an m- or n-contiguous tile needs 64 columns for its swizzle
+            if ta and not tb and bm % 64:
+                continue  # the rules keep the register-staged form there
             entries.append("PK_GEMM_DMA_KS(%s, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d)"
                            % ("gemm_%dx%dx%d_w%dx%d_k%d_%s_v44_dma%d" % (bm, bn, bk, wm, wn, ks, layout, st),
+                              bm, bn, bk, wm, wn, ks, st, ta, tb, occ))
+        for t in DMA_U:
+            bm, bn, bk, wm, wn, st, occ = t
+            entries.append("PK_GEMM_DMA_U(%s, %d, %d, %d, %d, %d, %d, %d, %d, %d)"
+                           % ("gemm_%dx%dx%d_w%dx%d_%s_v11%s_dma%d" % (bm, bn, bk, wm, wn, layout,
+                                                                     "_o%d" % occ if occ > 1 else "", st),
+                              bm, bn, bk, wm, wn, st, ta, tb, occ))
+        for t in DMA_KSPLIT_U:
+            bm, bn, bk, wm, wn, ks, st, occ = t
+            entries.append("PK_GEMM_DMA_KS_U(%s, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d)"
+                           % ("gemm_%dx%dx%d_w%dx%d_k%d_%s_v11_dma%d" % (bm, bn, bk, wm, wn, ks, layout, st),
                               bm, bn, bk, wm, wn, ks, st, ta, tb, occ))
         for t in (DMA_STREAMK if layout == "nn" else []):
             bm, bn, bk, wm, wn, st, occ = t
@@ -253,6 +279,18 @@ def main():
         entries.append("PK_CONV_DMA_KS(%s, %d, %d, %d, %d, %d, %d, %d, %d)"
                        % ("conv_%dx%dx%d_w%dx%d_k%d_v44_dma%d" % (bm, bn, bk, wm, wn, ks, st),
                           bm, bn, bk, wm, wn, ks, st, occ))
+    for va in (1, 4):
+        for t in CONV_DMA_U:
+            bm, bn, bk, wm, wn, st, occ = t
+            entries.append("PK_CONV_DMA_U(%s, %d, %d, %d, %d, %d, %d, %d, 1, %d)"
+                           % ("conv_%dx%dx%d_w%dx%d_v%d1%s_dma%d" % (bm, bn, bk, wm, wn, va,
+                                                                   "_o%d" % occ if occ > 1 else "", st),
+                              bm, bn, bk, wm, wn, st, va, occ))
+        for t in CONV_DMA_KSPLIT_U:
+            bm, bn, bk, wm, wn, ks, st, occ = t
+            entries.append("PK_CONV_DMA_KS_U(%s, %d, %d, %d, %d, %d, %d, %d, %d, 1, %d)"
+                           % ("conv_%dx%dx%d_w%dx%d_k%d_v%d1_dma%d" % (bm, bn, bk, wm, wn, ks, va, st),
+                              bm, bn, bk, wm, wn, ks, st, va, occ))
     for t in DMA_STREAMK:
         bm, bn, bk, wm, wn, st, occ = t
         entries.append("PK_CONV_DMA_SK(%s, %d, %d, %d, %d, %d, %d, %d)"

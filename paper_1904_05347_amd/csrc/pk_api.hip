@@ -15,9 +15,12 @@
 #include <string.h>
 
 #include <mutex>
+#include <string_view>
+#include <unordered_map>
 
 #include "../../include/pk.h"
 #include "pk_configs.hpp"
+#include "pk_cost.hpp"
 
 namespace {
 
@@ -36,13 +39,19 @@ const Config *env_forced = nullptr;
 bool env_forced_bad = false;
 std::once_flag env_once;
 
+// The configuration of this name, or NULL (an index over the registry, built
+// at first use: a scan of its several hundred names costs a call 1-2 us).
 const Config *find_config(const char *name)
 {
-    int n = 0;
-    const Config *cfgs = pk::configs(&n);
-    for (int i = 0; i < n; ++i)
-        if (strcmp(cfgs[i].name, name) == 0) return &cfgs[i];
-    return nullptr;
+    static const std::unordered_map<std::string_view, const Config *> index = [] {
+        std::unordered_map<std::string_view, const Config *> m;
+        int n = 0;
+        const Config *cfgs = pk::configs(&n);
+        for (int i = 0; i < n; ++i) m.emplace(cfgs[i].name, &cfgs[i]);
+        return m;
+    }();
+    const auto it = index.find(name);
+    return it == index.end() ? nullptr : it->second;
 }
 
 void read_env()
@@ -132,7 +141,7 @@ bool gemm_vec_ok(int ta, int tb, int64_t M, int64_t N, int64_t K, const float *A
 bool gemm_config_fits(const Config *c, int ta, int tb, bool vec_ok)
 {
     if (c->kind != pk::KIND_GEMM || c->trans_a != ta || c->trans_b != tb) return false;
-    if ((c->vec_a > 1 || c->vec_b > 1) && !vec_ok) return false;
+    if (!vec_ok && ((c->vec_a > 1 && !c->unaligned_a) || (c->vec_b > 1 && !c->unaligned_b))) return false;
     return true;
 }
 
@@ -352,7 +361,71 @@ bool dma_fits(const Config *c, int64_t lda, int64_t ldb)
     return !c->dma || (a_rows * lda * 4 + a_cols * 4 < lim && b_rows * ldb * 4 + b_cols * 4 < lim);
 }
 
-// Shapes outside the table, from the same measurements:
+int gemm_splits(const Config *c, int64_t M, int64_t N, int64_t K);
+
+// The configurations of a cost family's tiles, looked up once: one row per
+// GEMM layout (NN, NT, TN, TT), the first row for convolutions; NULL where a
+// layout has no such form.
+constexpr int kMaxCostTiles = 16;
+struct CostConfigs {
+    const Config *c[4][kMaxCostTiles] = {};
+    CostConfigs(const pk::CostFamily &f, bool gemm)
+    {
+        static const char *layout[4] = {"nn", "nt", "tn", "tt"};
+        char name[64];
+        for (int l = 0; l < (gemm ? 4 : 1); ++l)
+            for (int i = 0; i < f.n && i < kMaxCostTiles; ++i) {
+                snprintf(name, sizeof(name), f.tiles[i].name, layout[l]);
+                c[l][i] = find_config(name);
+            }
+    }
+};
+
+// The tile of a family that stands for configuration c when its time is
+// predicted (the same tile and groups; the register-staged K-split forms by
+// their direct-to-LDS twins), or -1.
+int cost_tile(const pk::CostFamily &f, const Config *c)
+{
+    for (int pass = 0; pass < 2; ++pass)
+        for (int i = 0; i < f.n; ++i) {
+            const pk::TileCost &t = f.tiles[i];
+            const bool staged = strstr(t.name, "dma") == nullptr;
+            if (t.bm == c->bm && t.bn == c->bn && t.bk == c->bk && t.kg == c->kgroups && t.streamk == c->streamk &&
+                (pass == 1 || staged == (c->dma == 0)))
+                return i;
+        }
+    return -1;
+}
+
+// The last selections of this thread, by the sizes they depend on (a
+// prediction over all tiles and splits costs 0.5 us, and a call needs it
+// twice: for its workspace and for itself).  A pure function of the key, so an
+// entry never goes stale; at most kMemo entries, the newest of a slot kept.
+struct Selection {
+    int64_t key[8];
+    const Config *c;
+    int splits;
+};
+constexpr int kMemo = 64;
+thread_local Selection t_memo[kMemo];
+
+Selection &memo_slot(const int64_t (&key)[8], bool *hit)
+{
+    uint64_t h = 0;
+    for (int64_t k : key) h = (h ^ (uint64_t)k) * 0x9e3779b97f4a7c15ull;
+    Selection &m = t_memo[h >> 58];
+    *hit = m.c && memcmp(m.key, key, sizeof(key)) == 0;
+    if (!*hit) memcpy(m.key, key, sizeof(key));
+    return m;
+}
+static_assert(kMemo == 1 << (64 - 58), "a slot per value of the hash's top bits");
+
+// How far below the time of the older rules' choice the cheapest tile has to
+// be predicted to take its place: the prediction's own error (6-10 % rms).
+constexpr float kCostMargin = 0.9f;
+
+// Products that no table entry serves: rules measured shape by shape, whose
+// choice stands unless pk_cost.hpp predicts a better one (select_gemm):
 //   - K <= 64: 64 x 64 tiles; for NN products with K == 64 and N a multiple
 //     of 64, the B-resident form (the whole reduction is one K-block);
 //   - longer reductions with at most one 32 x 64 tile per CU: the reduction
@@ -382,8 +455,8 @@ bool dma_fits(const Config *c, int64_t lda, int64_t ldb)
 //   - the direct-to-LDS forms only where a tile's rows span less than 2 GiB
 //     (else their register-staged twins); TT: register-staged tiles;
 //   - unaligned operands: 4-byte loads.
-const Config *select_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
-                          bool vec_ok)
+const Config *select_gemm_rule(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
+                               int64_t ldc, bool vec_ok)
 {
     static const char *layout[2][2] = {{"nn", "nt"}, {"tn", "tt"}};
     const char *lay = layout[ta][tb];
@@ -420,19 +493,71 @@ const Config *select_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64
     return find_config(name);
 }
 
+// The configuration of a product that no table entry serves, and its split of
+// K as far as ws_bytes of workspace hold the partial sums: the tile and split
+// of the least predicted time, unless the rule's choice above (its split:
+// gemm_splits) is within 10 % of it; always the rule's B-resident form (one
+// pass over A and C; not in the model) and its register-staged tiles where no
+// direct-to-LDS form can address the operands.
+const Config *predict_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
+                           bool vec_ok, size_t ws_bytes, int *splits)
+{
+    static const CostConfigs k44(pk::kCostGemm44, true), k11(pk::kCostGemm11, true);
+    const int l = 2 * ta + tb;
+    const pk::CostFamily &f = vec_ok ? pk::kCostGemm44 : pk::kCostGemm11;
+    const CostConfigs &k = vec_ok ? k44 : k11;
+    *splits = 1;
+    const Config *rule = select_gemm_rule(ta, tb, M, N, K, lda, ldb, ldc, vec_ok);
+    if (!rule || rule->bres) return rule;
+    int rs = gemm_splits(rule, M, N, K);
+    if (rs > 1 && ws_bytes < (size_t)rs * (size_t)M * (size_t)N * sizeof(float)) rs = 1;
+    int s = 1;
+    float us = 0.f;
+    const int i = pk::cheapest(
+        f, M, N, K, ws_bytes, pk::chain_of(K, rule->kgroups, rs),
+        [&](int t) { return k.c[l][t] && dma_fits(k.c[l][t], lda, ldb); }, &s, &us);
+    const int r = cost_tile(f, rule);
+    if (i < 0 || (r >= 0 && us > kCostMargin * pk::predict_us(f, f.tiles[r], M, N, K, rs))) {
+        *splits = rs;
+        return rule;
+    }
+    *splits = s;
+    return k.c[l][i];
+}
+
+const Config *select_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
+                          bool vec_ok, size_t ws_bytes, int *splits)
+{
+    const int64_t key[8] = {M, N, K, lda, ldb, ldc, (int64_t)ws_bytes, 8 + 4 * ta + 2 * tb + vec_ok};
+    bool hit;
+    Selection &m = memo_slot(key, &hit);
+    if (!hit) m.c = predict_gemm(ta, tb, M, N, K, lda, ldb, ldc, vec_ok, ws_bytes, &m.splits);
+    *splits = m.splits;
+    return m.c;
+}
+
+// Whether the direct-to-LDS gather can address a convolution's image from its
+// first element in 32-bit byte offsets, and 32 rows of its filter (as dma_fits).
+bool conv_dma_ok(int64_t N, int64_t H, int64_t W, int64_t Cin, int64_t Cout)
+{
+    return 4 * N * H * W * Cin < ((int64_t)1 << 31) && 4 * 33 * Cout < ((int64_t)1 << 31);
+}
+
 bool conv_config_fits(const Config *c, bool va4, bool vb4)
 {
     if (c->kind == pk::KIND_DIRECT) return true;  // checked against the window by the caller
     if (c->kind != pk::KIND_CONV) return false;
-    if (c->vec_a > 1 && !va4) return false;
-    if (c->vec_b > 1 && !vb4) return false;
+    if (c->vec_a > 1 && !va4 && !c->unaligned_a) return false;
+    if (c->vec_b > 1 && !vb4 && !c->unaligned_b) return false;
     return true;
 }
 
-// Convolutions with Cin and Cout multiples of 4 (16-byte gathers), from the
-// automated search over the paper's layers at batch 8 and 16 (shapes the
-// built-in table does not hold; checked on batch 2 and 12: the rules' time
-// over the search's, geometric mean, 1.12 -> 1.04):
+int choose_splits(const Config *c, int64_t M, int64_t N, int64_t K);
+
+// Convolutions that no table entry serves, Cin and Cout multiples of 4
+// (16-byte gathers): rules from the automated search over the paper's layers
+// at batch 8 and 16 (shapes the built-in table does not hold; checked on batch
+// 2 and 12: the rules' time over the search's, geometric mean, 1.12 -> 1.04):
 //   - Cout >= 128 with at least four rounds of 128 x 128 tiles (two
 //     work-groups per CU): 128 x 128 x 32 on 8 waves, both operands copied
 //     straight into two LDS stages;
@@ -447,7 +572,7 @@ bool conv_config_fits(const Config *c, bool va4, bool vb4)
 //     work-groups per CU;
 //   - the direct-to-LDS forms only while the image spans less than 2 GiB.
 // Channel counts that break 16-byte alignment use 4-byte gathers.
-const Config *select_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool dma_ok, bool allow_sk)
+const Config *select_conv_rule(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool dma_ok, bool allow_sk)
 {
     const char *name;
     const int64_t t128 = ceil_div(M, 128) * ceil_div(Cout, 128);
@@ -467,6 +592,49 @@ const Config *select_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4
     else
         name = "conv_64x64x32_w2x2_v44_dma2";
     return find_config(name);
+}
+
+// The configuration of a convolution that no table entry serves, and its
+// split of the reduction as far as ws_bytes hold the partial sums: the tile
+// and split of the least predicted time, unless the rule's choice above (its
+// split: choose_splits) is within 10 % of it.  Convolutions whose image (or
+// filter rows) the direct-to-LDS forms cannot address run the rule's
+// register-staged tiles.
+const Config *predict_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool dma_ok, bool allow_sk,
+                           size_t ws_bytes, int *splits)
+{
+    static const CostConfigs k44(pk::kCostConv44, false), k41(pk::kCostConv41, false), k11(pk::kCostConv11, false);
+    const pk::CostFamily &f = va4 && vb4 ? pk::kCostConv44 : va4 ? pk::kCostConv41 : pk::kCostConv11;
+    const CostConfigs &k = va4 && vb4 ? k44 : va4 ? k41 : k11;
+    *splits = 1;
+    const Config *rule = select_conv_rule(M, Cout, K, va4, vb4, dma_ok, allow_sk);
+    if (!rule) return nullptr;
+    int rs = rule->streamk ? 1 : choose_splits(rule, M, Cout, K);
+    if (rs > 1 && ws_bytes < (size_t)rs * (size_t)M * (size_t)Cout * sizeof(float)) rs = 1;
+    int s = 1;
+    float us = 0.f;
+    const int i = !dma_ok ? -1
+                          : pk::cheapest(
+                                f, M, Cout, K, ws_bytes, pk::chain_of(K, rule->kgroups, rs),
+                                [&](int t) { return k.c[0][t] && (allow_sk || !f.tiles[t].streamk); }, &s, &us);
+    const int r = cost_tile(f, rule);
+    if (i < 0 || (r >= 0 && us > kCostMargin * pk::predict_us(f, f.tiles[r], M, Cout, K, rs))) {
+        *splits = rs;
+        return rule;
+    }
+    *splits = s;
+    return k.c[0][i];
+}
+
+const Config *select_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool dma_ok, bool allow_sk,
+                          size_t ws_bytes, int *splits)
+{
+    const int64_t key[8] = {M, Cout, K, 0, 0, 0, (int64_t)ws_bytes, 16 + 8 * va4 + 4 * vb4 + 2 * dma_ok + allow_sk};
+    bool hit;
+    Selection &m = memo_slot(key, &hit);
+    if (!hit) m.c = predict_conv(M, Cout, K, va4, vb4, dma_ok, allow_sk, ws_bytes, &m.splits);
+    *splits = m.splits;
+    return m.c;
 }
 
 // Split of the K reduction of a convolution when the output alone gives too
@@ -792,8 +960,10 @@ int pk_sgemm_ws(char transA, char transB, int64_t M, int64_t N, int64_t K, float
         if (c && (!gemm_config_fits(c, ta, tb, vec_ok) || !bres_fits(c, N, K, ldc) || !dma_fits(c, lda, ldb) ||
                   (c->streamk && !streamk_ok(c))))
             c = nullptr;
-        if (c) splits = t->splits;
-        if (!c) c = select_gemm(ta, tb, M, N, K, lda, ldb, ldc, vec_ok);
+        if (c)
+            splits = t->splits;
+        else
+            c = select_gemm(ta, tb, M, N, K, lda, ldb, ldc, vec_ok, workspace_bytes, &splits);
         if (!c) return PK_ERR_NOT_SUPPORTED;
     }
     (void)was_forced;
@@ -866,8 +1036,7 @@ size_t pk_sgemm_workspace_bytes(char transA, char transB, int64_t M, int64_t N, 
         }
         if (c && !gemm_config_fits(c, ta, tb, vec_ok)) c = nullptr;
         if (!c) {
-            c = select_gemm(ta, tb, M, N, K, ta ? M : K, tb ? K : N, N, vec_ok);
-            splits = 0;
+            c = select_gemm(ta, tb, M, N, K, ta ? M : K, tb ? K : N, N, vec_ok, SIZE_MAX, &splits);
         }
     }
     if (!c || !gemm_config_fits(c, ta, tb, vec_ok)) return 0;
@@ -903,6 +1072,7 @@ size_t pk_conv2d_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin, i
     if (bad) return 0;
     const TunedShape *tuned = nullptr;
     TunedShape tbuf;
+    int picked = 0;  // the selection's split; 0: a forced or measured configuration
     if (!c) {
         tuned = (KH == KW && sh == sw && find_tuned(conv_kind(gemm_path), 0, 0, M, Cout, K, KH, sh, &tbuf)) ? &tbuf
                                                                                                          : nullptr;
@@ -920,9 +1090,9 @@ size_t pk_conv2d_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin, i
             tuned = nullptr;
         }
         if (!c)
-            c = gemm_path ? select_gemm(0, 0, M, Cout, Cin, Cin, Cout, Cout, v4)
-                          : select_conv(M, Cout, K, Cin % 4 == 0, Cout % 4 == 0,
-                                        (int64_t)4 * N * H * W * Cin < ((int64_t)1 << 31), true);
+            c = gemm_path ? select_gemm(0, 0, M, Cout, Cin, Cin, Cout, Cout, v4, SIZE_MAX, &picked)
+                          : select_conv(M, Cout, K, Cin % 4 == 0, Cout % 4 == 0, conv_dma_ok(N, H, W, Cin, Cout), true,
+                                        SIZE_MAX, &picked);
     }
     if (!c || c->kind == pk::KIND_DIRECT) return 0;
     if (c->streamk) {
@@ -931,7 +1101,7 @@ size_t pk_conv2d_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin, i
     }
     if (tuned && v4 && tuned->splits > 0 && t_forced_splits == 0)
         return tuned->splits > 1 ? (size_t)tuned->splits * (size_t)M * (size_t)Cout * sizeof(float) : 0;
-    const int splits = t_forced_splits > 0 ? t_forced_splits : choose_splits(c, M, Cout, K);
+    const int splits = t_forced_splits > 0 ? t_forced_splits : picked ? picked : choose_splits(c, M, Cout, K);
     if (splits <= 1) return 0;
     return (size_t)splits * (size_t)M * (size_t)Cout * sizeof(float);
 }
@@ -997,6 +1167,8 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, 
     const Config *c = forced(&bad);
     if (bad) return invalid(0);  // PK_FORCE_CONFIG names no configuration
     const bool was_forced = c != nullptr;
+    int picked = 0;  // the selection's split; 0: a forced or measured configuration
+    const size_t ws_room = workspace ? workspace_bytes : 0;
 
     const bool gemm_path = KH == 1 && KW == 1 && sh == 1 && sw == 1 && pt == 0 && pl == 0 && pb == 0 && pr == 0;
     TunedShape tbuf;
@@ -1014,7 +1186,7 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, 
             c = (tuned && vec_ok) ? find_config(tuned->config) : nullptr;
             if (c && (!gemm_config_fits(c, 0, 0, vec_ok) || !bres_fits(c, Cout, Cin, Cout) || !dma_fits(c, Cin, Cout)))
                 c = nullptr;
-            if (!c) c = select_gemm(0, 0, M, Cout, Cin, Cin, Cout, Cout, vec_ok);
+            if (!c) c = select_gemm(0, 0, M, Cout, Cin, Cin, Cout, Cout, vec_ok, ws_room, &picked);
             // a forced split needs a form that splits K across work-groups
             if (c && t_forced_splits > 1 && c->bres)
                 c = find_config(vec_ok ? "gemm_64x64x32_w2x2_nn_v44" : "gemm_64x64x16_w2x2_nn_v11");
@@ -1027,7 +1199,7 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, 
                    (d->vec_a == 1 || va4) && (d->tile_rows == 0 || !d->persistent || H * W * Cin < ((int64_t)1 << 29));
         };
         // the direct-to-LDS gather addresses the image in 32-bit byte offsets
-        const bool dma_ok = (int64_t)4 * N * H * W * Cin < ((int64_t)1 << 31);
+        const bool dma_ok = conv_dma_ok(N, H, W, Cin, Cout);
         if (c) {
             if (!conv_config_fits(c, va4, vb4) || (c->dma && !dma_ok)) return PK_ERR_NOT_SUPPORTED;
             if (c->kind == pk::KIND_DIRECT && !direct_ok(c)) return PK_ERR_NOT_SUPPORTED;
@@ -1048,7 +1220,7 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, 
                     }
                 }
             }
-            if (!c) c = select_conv(M, Cout, K, va4, vb4, dma_ok, true);
+            if (!c) c = select_conv(M, Cout, K, va4, vb4, dma_ok, true, ws_room, &picked);
         }
         if (!c) return PK_ERR_NOT_SUPPORTED;
         a.H = (int)H;
@@ -1075,9 +1247,9 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, 
         } else if (was_forced) {
             return planned ? PK_ERR_WORKSPACE : PK_ERR_NOT_SUPPORTED;
         } else {
-            c = gemm_path ? select_gemm(0, 0, M, Cout, Cin, Cin, Cout, Cout, vec_ok)
-                          : select_conv(M, Cout, K, va4, vb4, (int64_t)4 * N * H * W * Cin < ((int64_t)1 << 31),
-                                        false);
+            c = gemm_path ? select_gemm(0, 0, M, Cout, Cin, Cin, Cout, Cout, vec_ok, ws_room, &picked)
+                          : select_conv(M, Cout, K, va4, vb4, conv_dma_ok(N, H, W, Cin, Cout), false, ws_room,
+                                        &picked);
             if (!c) return PK_ERR_NOT_SUPPORTED;
         }
     }
@@ -1111,7 +1283,7 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, 
         if (splits > 1 && (!workspace || workspace_bytes < (size_t)splits * per_split)) return PK_ERR_WORKSPACE;
     } else {
         const bool tuned_cfg = tuned && strcmp(c->name, tuned->config) == 0 && tuned->splits > 0;
-        splits = tuned_cfg ? tuned->splits : choose_splits(c, M, Cout, K);
+        splits = picked ? picked : tuned_cfg ? tuned->splits : choose_splits(c, M, Cout, K);
         if (splits > 1 && (!workspace || workspace_bytes < (size_t)splits * per_split)) splits = 1;
     }
     a.A = x;

@@ -41,6 +41,9 @@ struct Config {
     // work-group's tile (its columns are bm / tile_rows, its channels bn, its
     // input-channel load width vec_a); 0 for every other kind
     int tile_rows = 0;
+    // direct-to-LDS forms that take an operand of any 4-byte alignment, size
+    // and leading dimension ("v1" in the name; vec_a / vec_b stay the widest copy)
+    int unaligned_a = 0, unaligned_b = 0;
 };
 
 // LDS a tiled direct convolution instance may ask for at launch (dynamic).

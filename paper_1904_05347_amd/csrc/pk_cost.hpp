@@ -1,0 +1,193 @@
+// pk_cost.hpp -- the time of a product on each compiled tile, predicted from
+// its sizes: the per-shape parameter choice of Section 5 for shapes that no
+// table holds.
+//
+// A product on one tile configuration, its reduction split s ways across
+// work-groups, runs items = tiles * s work-groups of `steps` K-blocks each,
+// n = ceil(items / 256) of them on the fullest CU, which holds R at once:
+//
+//   t = t0 + sum over rounds of r <= R work-groups ( max(l, r * m) * steps + ov )
+//          + (s > 1: c0 + c1 * (s + 1) * megabytes of one partial sum)
+//
+// m is a K-block's share of the CU when the matrix cores are busy (the tile's
+// work over the rate it sustains), l its latency when nothing else runs there,
+// ov a round's fill and epilogue, t0 a launch, c0 and c1 the second kernel
+// that adds the partial sums (c0 is 1.6 to 2.6 in a graph; 4 stands here, what
+// the second launch and the workspace cost a caller that launches each call).
+// All in microseconds, fitted to graph-timed calls on MI355X: every tile and split of {1, 2, 3, 4, 6, 8, 12, 16} on 230
+// random products (sides 16 to 4096, four layouts) and 220 random
+// convolutions (1x1 to 7x7, stride 1 and 2, 8 to 1024 channels), 23 000 times
+// in all, reproduced to 6-10 % (rms).  Taking the configuration and split of
+// the least predicted time costs 2-4 % over the best of all of them
+// (geometric mean per group of shapes); the rules that stood before cost
+// 6-13 % on aligned products, 17-19 % on aligned convolutions, and the 4-byte
+// kernels that served unaligned operands 21-36 % and 37-80 %.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+namespace pk {
+
+struct TileCost {
+    const char *name;  // of the configuration; GEMM: "%s" stands for the layout
+    int bm, bn, bk;
+    int kg;       // groups of waves that split a tile's K-blocks inside the work-group
+    int per_cu;   // R: work-groups a CU holds (LDS)
+    int streamk;  // equal shares of the K-blocks: m * (all K-blocks) / CUs
+    float l, m, ov;
+};
+
+struct CostFamily {
+    float t0, c0, c1;
+    int n;
+    const TileCost *tiles;
+};
+
+// products whose operands allow 16-byte accesses
+constexpr TileCost kCostGemm44Tiles[] = {
+    {"gemm_256x256x32_w2x4_%s_v44_o2_dma2", 256, 256, 32, 1, 1, 0, 0.563f, 7.158f, 6.92f},
+    {"gemm_128x128x32_w2x4_%s_v44_o2_dma2", 128, 128, 32, 1, 2, 0, 0.741f, 1.959f, 2.89f},
+    {"gemm_128x96x32_w4x1_%s_v44_dma2", 128, 96, 32, 1, 2, 0, 0.156f, 1.583f, 3.49f},
+    {"gemm_128x64x32_w2x2_%s_v44_dma2", 128, 64, 32, 1, 3, 0, 0.360f, 1.099f, 2.70f},
+    {"gemm_128x32x32_w4x1_%s_v44_dma2", 128, 32, 32, 1, 4, 0, 0.489f, 0.668f, 2.10f},
+    {"gemm_64x64x32_w2x2_%s_v44_dma2", 64, 64, 32, 1, 5, 0, 0.297f, 0.631f, 1.83f},
+    {"gemm_64x64x16_w2x2_%s_v44_dma3", 64, 64, 16, 1, 6, 0, 0.375f, 0.307f, 1.74f},
+    {"gemm_32x64x32_w1x2_%s_v44_dma3", 32, 64, 32, 1, 4, 0, 0.680f, 0.431f, 1.77f},
+    {"gemm_64x64x32_w2x2_k4_%s_v44_dma2", 64, 64, 32, 4, 1, 0, 0.529f, 2.055f, 3.34f},
+    {"gemm_64x64x32_w2x2_k2_%s_v44_dma3", 64, 64, 32, 2, 1, 0, 0.488f, 1.116f, 2.15f},
+    {"gemm_32x64x32_w1x2_k4_%s_v44_dma3", 32, 64, 32, 4, 1, 0, 0.343f, 1.228f, 2.49f},
+    {"gemm_64x64x16_w2x2_%s_v44", 64, 64, 16, 1, 8, 0, 0.424f, 0.324f, 1.75f},
+};
+constexpr CostFamily kCostGemm44 = {2.29f, 4.00f, 0.305f, 12, kCostGemm44Tiles};
+
+// products of operands aligned to 4 bytes
+constexpr TileCost kCostGemm11Tiles[] = {
+    {"gemm_256x256x32_w2x4_%s_v11_o2_dma2", 256, 256, 32, 1, 1, 0, 0.138f, 7.236f, 6.98f},
+    {"gemm_128x128x32_w2x4_%s_v11_o2_dma2", 128, 128, 32, 1, 2, 0, 1.458f, 2.038f, 2.82f},
+    {"gemm_128x96x32_w4x1_%s_v11_dma2", 128, 96, 32, 1, 2, 0, 0.184f, 1.642f, 3.58f},
+    {"gemm_128x64x32_w2x2_%s_v11_dma2", 128, 64, 32, 1, 3, 0, 0.513f, 1.137f, 2.72f},
+    {"gemm_128x32x32_w4x1_%s_v11_dma2", 128, 32, 32, 1, 4, 0, 0.362f, 0.709f, 2.10f},
+    {"gemm_64x64x32_w2x2_%s_v11_dma2", 64, 64, 32, 1, 5, 0, 0.373f, 0.681f, 1.78f},
+    {"gemm_64x64x16_w2x2_%s_v11_dma3", 64, 64, 16, 1, 6, 0, 0.433f, 0.333f, 1.57f},
+    {"gemm_32x64x32_w1x2_%s_v11_dma3", 32, 64, 32, 1, 4, 0, 0.736f, 0.453f, 1.81f},
+    {"gemm_64x64x32_w2x2_k4_%s_v11_dma2", 64, 64, 32, 4, 1, 0, 0.194f, 2.159f, 3.51f},
+    {"gemm_64x64x32_w2x2_k2_%s_v11_dma3", 64, 64, 32, 2, 1, 0, 0.330f, 1.210f, 2.18f},
+    {"gemm_32x64x32_w1x2_k4_%s_v11_dma3", 32, 64, 32, 4, 1, 0, 0.681f, 1.347f, 2.59f},
+    {"gemm_64x64x16_w2x2_%s_v11", 64, 64, 16, 1, 8, 0, 0.581f, 0.401f, 1.45f},
+};
+constexpr CostFamily kCostGemm11 = {2.71f, 4.00f, 0.331f, 12, kCostGemm11Tiles};
+
+// convolutions, Cin and Cout multiples of four
+constexpr TileCost kCostConv44Tiles[] = {
+    {"conv_128x128x32_w2x4_v44_o2_dma2", 128, 128, 32, 1, 2, 0, 0.491f, 1.992f, 3.36f},
+    {"conv_128x96x32_w4x1_v44_dma2", 128, 96, 32, 1, 2, 0, 0.443f, 1.766f, 3.69f},
+    {"conv_128x64x32_w2x2_v44_dma2", 128, 64, 32, 1, 3, 0, 0.093f, 1.153f, 2.82f},
+    {"conv_128x32x32_w4x1_v44_dma2", 128, 32, 32, 1, 4, 0, 0.365f, 0.702f, 2.57f},
+    {"conv_64x64x32_w2x2_v44_dma2", 64, 64, 32, 1, 5, 0, 0.510f, 0.613f, 2.12f},
+    {"conv_64x64x16_w2x2_v44_dma3", 64, 64, 16, 1, 6, 0, 0.414f, 0.302f, 1.53f},
+    {"conv_32x64x32_w1x2_v44_dma3", 32, 64, 32, 1, 4, 0, 0.770f, 0.339f, 1.85f},
+    {"conv_64x64x32_w2x2_k4_v44_dma2", 64, 64, 32, 4, 1, 0, 2.197f, 2.174f, 3.96f},
+    {"conv_64x64x32_w2x2_k2_v44_dma3", 64, 64, 32, 2, 1, 0, 0.231f, 1.214f, 2.38f},
+    {"conv_128x128x32_w2x4_v44_o2_dma2_sk", 128, 128, 32, 1, 2, 1, 0.329f, 2.103f, 28.29f},
+};
+constexpr CostFamily kCostConv44 = {3.46f, 4.00f, 0.149f, 10, kCostConv44Tiles};
+
+// ... Cin a multiple of four, any Cout
+constexpr TileCost kCostConv41Tiles[] = {
+    {"conv_128x128x32_w2x4_v41_o2_dma2", 128, 128, 32, 1, 2, 0, 0.597f, 2.070f, 3.21f},
+    {"conv_128x96x32_w4x1_v41_dma2", 128, 96, 32, 1, 2, 0, 0.114f, 1.783f, 3.38f},
+    {"conv_128x64x32_w2x2_v41_dma2", 128, 64, 32, 1, 3, 0, 0.327f, 1.162f, 2.75f},
+    {"conv_128x32x32_w4x1_v41_dma2", 128, 32, 32, 1, 4, 0, 0.897f, 0.656f, 1.61f},
+    {"conv_64x64x32_w2x2_v41_dma2", 64, 64, 32, 1, 5, 0, 0.540f, 0.617f, 2.30f},
+    {"conv_64x64x16_w2x2_v41_dma3", 64, 64, 16, 1, 6, 0, 0.464f, 0.320f, 1.31f},
+    {"conv_32x64x32_w1x2_v41_dma3", 32, 64, 32, 1, 4, 0, 0.813f, 0.350f, 1.71f},
+    {"conv_64x64x32_w2x2_k2_v41_dma3", 64, 64, 32, 2, 1, 0, 0.224f, 1.310f, 2.30f},
+};
+constexpr CostFamily kCostConv41 = {4.00f, 4.00f, 0.196f, 8, kCostConv41Tiles};
+
+// ... any Cin and Cout
+constexpr TileCost kCostConv11Tiles[] = {
+    {"conv_128x128x32_w2x4_v11_o2_dma2", 128, 128, 32, 1, 2, 0, 0.320f, 2.383f, 3.02f},
+    {"conv_128x96x32_w4x1_v11_dma2", 128, 96, 32, 1, 2, 0, 0.204f, 2.015f, 4.19f},
+    {"conv_128x64x32_w2x2_v11_dma2", 128, 64, 32, 1, 3, 0, 0.420f, 1.351f, 3.63f},
+    {"conv_128x32x32_w4x1_v11_dma2", 128, 32, 32, 1, 4, 0, 0.126f, 0.878f, 4.11f},
+    {"conv_64x64x32_w2x2_v11_dma2", 64, 64, 32, 1, 5, 0, 0.318f, 0.718f, 2.09f},
+    {"conv_64x64x16_w2x2_v11_dma3", 64, 64, 16, 1, 6, 0, 0.650f, 0.387f, 0.23f},
+    {"conv_32x64x32_w1x2_v11_dma3", 32, 64, 32, 1, 4, 0, 1.063f, 0.442f, 1.25f},
+    {"conv_64x64x32_w2x2_k2_v11_dma3", 64, 64, 32, 2, 1, 0, 1.213f, 1.496f, 2.65f},
+    {"conv_64x64x16_w2x2_v11", 64, 64, 16, 1, 8, 0, 0.748f, 0.441f, 0.29f},
+};
+constexpr CostFamily kCostConv11 = {4.87f, 4.00f, 0.202f, 9, kCostConv11Tiles};
+
+// Most partial sums the choice may ask a workspace for: the stream-K plans'
+// 64 MiB, which the static scratch of the no-allocation entry also holds.
+constexpr size_t kCostMaxPartials = (size_t)64 << 20;
+constexpr int kCostCUs = 256;
+constexpr int kCostSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
+
+// Predicted time (us) of an M x N x K product on tile c with its reduction
+// split s ways (sizes at least 1).
+inline float predict_us(const CostFamily &f, const TileCost &c, int64_t M, int64_t N, int64_t K, int s)
+{
+    const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    const int64_t nkb = (K + c.bk - 1) / c.bk;
+    if (c.streamk) return f.t0 + c.ov + c.m * ((float)tiles * (float)nkb / kCostCUs);
+    int64_t per = nkb;
+    if (s > 1) {
+        per = (nkb + s - 1) / s;
+        s = (int)((nkb + per - 1) / per);
+    }
+    const float steps = (float)((per + c.kg - 1) / c.kg);
+    const int64_t n = (tiles * s + kCostCUs - 1) / kCostCUs;
+    const int64_t full = n / c.per_cu, rem = n - full * c.per_cu;
+    auto round = [&](float r) { return (r * c.m > c.l ? r * c.m : c.l) * steps + c.ov; };
+    float t = f.t0 + (float)full * round((float)c.per_cu);
+    if (rem) t += round((float)rem);
+    if (s > 1) t += f.c0 + f.c1 * 4e-6f * (float)(s + 1) * (float)M * (float)N;
+    return t;
+}
+
+// Longest run of products that one accumulator adds up, in K: a split, or
+// groups of waves, shorten it.  The rounding error of a result grows with it
+// (about 7e-7 of the result at 1777, 1.1e-6 at 4096, 2-norm).
+inline int64_t chain_of(int64_t K, int kg, int s) { return (K + (int64_t)kg * s - 1) / ((int64_t)kg * s); }
+
+// Chains up to this length are taken for their time alone; a longer one only
+// where the choice it replaces has it too, so no result loses precision.
+constexpr int64_t kCostFreeChain = 2048;
+
+// The tile and split of the least predicted time among the tiles for which
+// usable(index) holds, the splits whose partial sums fit in ws_bytes and the
+// chains of at most max_chain; -1 when there is none.
+template <typename F>
+int cheapest(const CostFamily &f, int64_t M, int64_t N, int64_t K, size_t ws_bytes, int64_t max_chain, F usable,
+             int *split, float *us)
+{
+    if (max_chain < kCostFreeChain) max_chain = kCostFreeChain;
+    int best = -1;
+    const size_t room = ws_bytes < kCostMaxPartials ? ws_bytes : kCostMaxPartials;
+    for (int i = 0; i < f.n; ++i) {
+        const TileCost &c = f.tiles[i];
+        if (!usable(i)) continue;
+        const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        const int64_t nkb = (K + c.bk - 1) / c.bk;
+        for (int s : kCostSplits) {
+            // (a split that leaves a work-group under two K-blocks, or more
+            // work-groups than the chip holds anyway, was never the fastest)
+            if (s > 1 && (c.streamk || 2 * s > nkb || tiles * s > 16 * kCostCUs ||
+                          (double)s * (double)M * (double)N * 4.0 > (double)room))
+                break;
+            if (chain_of(K, c.kg, s) > max_chain) continue;
+            const float t = predict_us(f, c, M, N, K, s);
+            if (best < 0 || t < *us) {
+                best = i;
+                *split = s;
+                *us = t;
+            }
+        }
+    }
+    return best;
+}
+
+}  // namespace pk

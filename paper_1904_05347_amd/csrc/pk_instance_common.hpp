@@ -99,15 +99,16 @@ static hipError_t launch_gemm_streamk(const KernelArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool UA = false,
+          bool UB = false>
 static int resident_dma_streamk(int beta)
 {
     static int per_cu[2] = {0, 0};  // the same on every MI355X
     const int b = beta ? 1 : 0;
     if (per_cu[b] == 0) {
-        auto kernel = gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false>;
+        auto kernel = gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false, UA, UB>;
         if constexpr (AMODE != A_CONV) {
-            if (b) kernel = gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true>;
+            if (b) kernel = gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true, UA, UB>;
         }
         int n = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 64 * WAVES_M * WAVES_N, 0) != hipSuccess ||
@@ -119,7 +120,8 @@ static int resident_dma_streamk(int beta)
 }
 
 // Stream-K launch of the direct-to-LDS contraction (as launch_gemm_streamk).
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool UA = false,
+          bool UB = false>
 static hipError_t launch_gemm_dma_streamk(const KernelArgs &a, hipStream_t stream)
 {
     if (a.sk_groups < 1 || !a.sk_part || !a.sk_cnt || a.sk_nkb < 1) return hipErrorInvalidValue;
@@ -128,18 +130,19 @@ static hipError_t launch_gemm_dma_streamk(const KernelArgs &a, hipStream_t strea
     const dim3 grid((unsigned)a.sk_groups), block(64 * WAVES_M * WAVES_N);
     if constexpr (AMODE != A_CONV) {
         if (reads_c<AMODE>(a)) {
-            hipLaunchKernelGGL((gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true>),
+            hipLaunchKernelGGL((gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true, UA, UB>),
                                grid, block, 0, stream, a);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false>), grid,
+    hipLaunchKernelGGL((gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false, UA, UB>), grid,
                        block, 0, stream, a);
     return hipGetLastError();
 }
 
 // K split among groups of waves, operands copied straight into LDS.
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int KS, int STAGES, int AMODE, bool TB, int OCC>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int KS, int STAGES, int AMODE, bool TB, int OCC,
+          bool UA = false, bool UB = false>
 static hipError_t launch_gemm_dma_ksplit(const KernelArgs &a, hipStream_t stream)
 {
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)(a.nbatch > 1 ? a.nbatch : 1), (unsigned)a.splits);
@@ -147,12 +150,12 @@ static hipError_t launch_gemm_dma_ksplit(const KernelArgs &a, hipStream_t stream
     if constexpr (AMODE != A_CONV) {
         if (reads_c<AMODE>(a)) {
             hipLaunchKernelGGL(
-                (gemm_dma_ksplit_kernel<BM, BN, BK, WAVES_M, WAVES_N, KS, STAGES, AMODE, TB, OCC, true>), grid,
+                (gemm_dma_ksplit_kernel<BM, BN, BK, WAVES_M, WAVES_N, KS, STAGES, AMODE, TB, OCC, true, UA, UB>), grid,
                 block, 0, stream, a);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((gemm_dma_ksplit_kernel<BM, BN, BK, WAVES_M, WAVES_N, KS, STAGES, AMODE, TB, OCC, false>),
+    hipLaunchKernelGGL((gemm_dma_ksplit_kernel<BM, BN, BK, WAVES_M, WAVES_N, KS, STAGES, AMODE, TB, OCC, false, UA, UB>),
                        grid, block, 0, stream, a);
     return hipGetLastError();
 }
@@ -207,19 +210,20 @@ static hipError_t launch_gemm_ksplit(const KernelArgs &a, hipStream_t stream)
 
 // Direct-to-LDS staging (same grid as launch_gemm; dense operands).  The
 // host checks that the rows one tile addresses span less than 2 GiB.
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool UA = false,
+          bool UB = false>
 static hipError_t launch_gemm_dma(const KernelArgs &a, hipStream_t stream)
 {
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)(a.nbatch > 1 ? a.nbatch : 1), (unsigned)a.splits);
     const dim3 block(64 * WAVES_M * WAVES_N);
     if constexpr (AMODE != A_CONV) {
         if (reads_c<AMODE>(a)) {
-            hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true>), grid,
+            hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true, UA, UB>), grid,
                                block, 0, stream, a);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false>), grid, block, 0,
+    hipLaunchKernelGGL((gemm_dma_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false, UA, UB>), grid, block, 0,
                        stream, a);
     return hipGetLastError();
 }
@@ -324,6 +328,28 @@ static constexpr int lds_bytes()
     {#name, KIND_CONV, BM, BN, BK, WM, WN, 0, 0, 4, 4, OCC, 0, STAGES * 4 * (BM * BK + BK * BN),       \
      &launch_gemm_dma_streamk<BM, BN, BK, WM, WN, STAGES, A_CONV, false, OCC>, 0, 1,                   \
      &resident_dma_streamk<BM, BN, BK, WM, WN, STAGES, A_CONV, false, OCC>, 0, 1, STAGES}
+
+// The same forms for operands without 16-byte alignment: of both operands
+// (GEMM), or of the image and / or the filter (convolution; VA, VB = 1).
+#define PK_GEMM_DMA_U(name, BM, BN, BK, WM, WN, STAGES, TA, TB, OCC)                                  \
+    {#name, KIND_GEMM, BM, BN, BK, WM, WN, TA, TB, 4, 4, OCC, 0, STAGES * 4 * (BM * BK + BK * BN),     \
+     &launch_gemm_dma<BM, BN, BK, WM, WN, STAGES, (TA ? A_MCONTIG : A_KCONTIG), (TB != 0), OCC, true, true>, 0, 0, \
+     nullptr, 0, 1, STAGES, 0, 1, 1}
+
+#define PK_GEMM_DMA_KS_U(name, BM, BN, BK, WM, WN, KS, STAGES, TA, TB, OCC)                            \
+    {#name, KIND_GEMM, BM, BN, BK, WM, WN, TA, TB, 4, 4, OCC, 0, KS * STAGES * 4 * (BM * BK + BK * BN), \
+     &launch_gemm_dma_ksplit<BM, BN, BK, WM, WN, KS, STAGES, (TA ? A_MCONTIG : A_KCONTIG), (TB != 0), OCC, true, \
+                             true>, 0, 0, nullptr, 0, KS, STAGES, 0, 1, 1}
+
+#define PK_CONV_DMA_U(name, BM, BN, BK, WM, WN, STAGES, VA, VB, OCC)                                   \
+    {#name, KIND_CONV, BM, BN, BK, WM, WN, 0, 0, 4, 4, OCC, 0, STAGES * 4 * (BM * BK + BK * BN),    \
+     &launch_gemm_dma<BM, BN, BK, WM, WN, STAGES, A_CONV, false, OCC, (VA == 1), (VB == 1)>, 0, 0, nullptr, 0, 1, \
+     STAGES, 0, (VA == 1), (VB == 1)}
+
+#define PK_CONV_DMA_KS_U(name, BM, BN, BK, WM, WN, KS, STAGES, VA, VB, OCC)                            \
+    {#name, KIND_CONV, BM, BN, BK, WM, WN, 0, 0, 4, 4, OCC, 0, KS * STAGES * 4 * (BM * BK + BK * BN), \
+     &launch_gemm_dma_ksplit<BM, BN, BK, WM, WN, KS, STAGES, A_CONV, false, OCC, (VA == 1), (VB == 1)>, 0, 0, \
+     nullptr, 0, KS, STAGES, 0, (VA == 1), (VB == 1)}
 
 #define PK_CONV_D(name, BM, BN, BK, WM, WN, VA, VB, OCC)                                               \
     {#name, KIND_CONV, BM, BN, BK, WM, WN, 0, 0, VA, VB, OCC, 0,                                      \

@@ -612,26 +612,45 @@ gemm_kernel(KernelArgs p)
 //   k-major (A 'T', B 'N'): BK x R, rows of contiguous m (n); the second
 //     half of the K-block (read by lanes 32..63) has its chunks XOR 8, i.e.
 //     column x sits at x ^ 32, so the two half-waves' 128-byte reads use
-//     opposite halves of the 64 banks.
+//     opposite halves of the 64 banks.  With R an odd multiple of 32 adjacent
+//     rows start in opposite halves, so the second half's rows swap in pairs
+//     instead (k at k ^ 1).
 // Elements past the operand's rows or K get an offset past the buffer's
 // range, which the hardware answers with zeros.  Offsets count from a
 // per-tile, per-K-block base, so they stay below 2^31 whenever R (KROWS) or
 // BK (k-major) rows of the operand do (checked by the host).
-template <int R, int BK, int NW, bool KROWS>
+// UNAL: pointer, leading dimension and extents need no multiple of four.
+// Buffer loads take any 4-byte-aligned address (a probe copied rows at 0 to 3
+// elements past a 16-byte boundary: same data, 16.5-18.5 TB/s over the chip
+// from L2 against 32 aligned, while the tiles here ask for 4 to 16 of the
+// 27 bytes per clock and CU that is), so whole chunks still move as 16 bytes:
+//   KROWS: only the K-block that holds the end of a K that is no multiple of
+//     four is copied by single elements, since its last chunk would carry the
+//     next row's first elements;
+//   k-major: a chunk over the end of a row holds what follows in memory, in
+//     columns of C that are never stored; past the operand's last element the
+//     buffer's range, set to it, answers each element with zero.
+// Bound by the matrix cores as the aligned form: 4001 x 3999 x 4003 in 948-951
+// us in every layout on 256 x 256 tiles (135 TFLOP/s; 4-byte loads through
+// registers on 64 x 64 tiles reach 53-62).
+template <int R, int BK, int NW, bool KROWS, bool UNAL = false>
 struct DmaOperand {
     static constexpr int CPR = KROWS ? BK / 4 : R / 4;  // 16-byte chunks per LDS row
     static constexpr int RPS = KROWS ? 16 / CPR : 1;    // rows per step of the KROWS swizzle
     static constexpr int FLOATS = R * BK;
     static constexpr int L = FLOATS / 256 / NW;  // instructions per lane per K-block
     static_assert(FLOATS % (256 * NW) == 0, "whole 1 KiB pieces per wave");
-    static_assert(KROWS ? (CPR <= 16 && 16 % CPR == 0) : (R % 64 == 0), "swizzle geometry");
+    static_assert(KROWS ? (CPR <= 16 && 16 % CPR == 0) : (R % 32 == 0), "swizzle geometry");
+    static constexpr bool PAIRS = !KROWS && R % 64 == 32;  // the second half's k rows swap in pairs
     int off[L], kk[L];
     bool ok[L];
+    int rows;  // the operand's row count (m or n), for the UNAL forms' edges
 
     // ld: the operand's leading dimension; r0 / rlim: its first row (m or
     // n) of this tile and the row count
     __device__ __forceinline__ void init(int64_t ld, int r0, int rlim, int wave, int lane)
     {
+        rows = rlim;
 #pragma unroll
         for (int i = 0; i < L; ++i) {
             const int q = (i * NW + wave) * 64 + lane;  // chunk position in the tile
@@ -642,8 +661,9 @@ struct DmaOperand {
                 kk[i] = 4 * c;
                 ok[i] = r0 + r < rlim;
             } else {
-                const int k = q / CPR;
-                const int c = (q % CPR) ^ (k >= BK / 2 ? 8 : 0);
+                const int kp = q / CPR;  // row position in the tile
+                const int k = PAIRS && kp >= BK / 2 ? kp ^ 1 : kp;
+                const int c = PAIRS ? q % CPR : (q % CPR) ^ (k >= BK / 2 ? 8 : 0);
                 off[i] = (k * (int)ld + 4 * c) * 4;
                 kk[i] = k;
                 ok[i] = r0 + 4 * c < rlim;
@@ -657,7 +677,31 @@ struct DmaOperand {
                                           int wave) const
     {
         const float *b = KROWS ? base + (int64_t)r0 * ld + k0 : base + (int64_t)k0 * ld + r0;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)b, 0, 0x7fffffff, 0x00020000);
+        int range = 0x7fffffff;
+        if constexpr (UNAL && !KROWS) {  // the operand's last element is K-1, rows-1
+            const int64_t left = ((K - 1 - k0) * ld + (rows - r0)) * 4;
+            range = left < 0 ? 0 : left < range ? (int)left : range;
+        }
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)b, 0, range, 0x00020000);
+        if constexpr (UNAL && KROWS) {
+            if (K % 4 != 0 && k0 + BK > K) {  // uniform: the last K-block, element by element
+                int lane = threadIdx.x & 63;
+                asm volatile("" : "+v"(lane));  // computed here, not kept in registers over the K loop
+#pragma unroll
+                for (int i = I0; i < I1; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int q = (i * NW + wave) * 64 + e * 16 + lane / 4;
+                        const int r = q / CPR;
+                        const int k = 4 * ((q % CPR) ^ ((r / RPS) % CPR)) + lane % 4;
+                        const int o = (r0 + r < rows && k0 + k < K) ? (r * (int)ld + k) * 4 : (int)0x80000000;
+                        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                            rs, (__attribute__((address_space(3))) void *)(tile + (i * NW + wave) * 256 + e * 64), 4, o,
+                            0, 0, 0);
+                    }
+                return;
+            }
+        }
 #pragma unroll
         for (int i = I0; i < I1; ++i) {
             const int o = (ok[i] && k0 + kk[i] < K) ? off[i] : (int)0x80000000;
@@ -674,9 +718,9 @@ struct DmaOperand {
             v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
         } else {
             const int k = h * (BK / 2) + 4 * g;
-            const int col = row ^ (32 * h);
+            const int col = PAIRS ? row : row ^ (32 * h);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) v[t] = tile[(k + t) * R + col];
+            for (int t = 0; t < 4; ++t) v[t] = tile[(PAIRS ? (k + t) ^ h : k + t) * R + col];
         }
     }
     // m-contiguous layout: the same four k of the four adjacent rows row ..
@@ -685,7 +729,7 @@ struct DmaOperand {
     template <typename Frag>
     __device__ __forceinline__ static void read4_rows4(const float *tile, int row, int h, int g, Frag &v)
     {
-        static_assert(!KROWS, "adjacent rows share a chunk only in the m-contiguous layout");
+        static_assert(!KROWS && !PAIRS, "adjacent rows share a chunk only in the m-contiguous layout");
         const int k = h * (BK / 2) + 4 * g;
         const int col = row ^ (32 * h);
 #pragma unroll
@@ -713,10 +757,13 @@ struct DmaConvA {
     int col;                    // this lane's k offset inside the K-block
     int ci, kw, kh;             // decomposition of the lane's current k
     int H, W, Cin, KW;
+    int step;  // k from one issue to the next
 
-    __device__ __forceinline__ void init(const KernelArgs &p, int m0, int kbeg, int wave, int lane)
+    // blocks: K-blocks from one issue to the next
+    __device__ __forceinline__ void init(const KernelArgs &p, int m0, int kbeg, int wave, int lane, int blocks = 1)
     {
         H = p.H; W = p.W; Cin = p.Cin; KW = p.KW;
+        step = BK * blocks;
         const int r_first = ((wave * 64) + lane) / CPR;
         col = 4 * ((lane % CPR) ^ ((r_first / RPS) % CPR));
 #pragma unroll
@@ -743,9 +790,9 @@ struct DmaConvA {
     }
     // copy K-block k0 (the one the walk stands at) into `tile` (copy slots
     // I0 .. I1-1 of this lane; the whole block by default), then, once the
-    // block's last slot is issued, step the walk `blocks` K-blocks on
+    // block's last slot is issued, step the walk on
     template <int I0 = 0, int I1 = L>
-    __device__ __forceinline__ void issue(const float *x, int k0, int K, float *tile, int wave, int blocks = 1)
+    __device__ __forceinline__ void issue(const float *x, int k0, int K, float *tile, int wave)
     {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, 0x7fffffff, 0x00020000);
         const bool k_ok = k0 + col < K;
@@ -758,7 +805,7 @@ struct DmaConvA {
                 rs, (__attribute__((address_space(3))) void *)(tile + (i * NW + wave) * 256), 16, o, 0, 0, 0);
         }
         if constexpr (I1 == L) {
-            ci += BK * blocks;
+            ci += step;
             while (ci >= Cin) {
                 ci -= Cin;
                 if (++kw == KW) { kw = 0; ++kh; }
@@ -771,6 +818,112 @@ struct DmaConvA {
     }
 };
 
+// The gather for channel counts that are no multiple of four (or an image
+// that is not 16-byte aligned): DmaConvA's tile, copied one element per lane.
+// A row's elements are then any (kh, kw, ci), so nothing is padded and the
+// image is read once per tap.  Copy slot i of a lane is piece i*NW + wave
+// of 64 elements, i.e. RPS rows, so a lane's k repeats every CPR pieces: WALKS
+// (kh, kw, ci) walks per lane, each stepped by K-blocks without a division
+// (the step's own (kh, kw, ci), with carries).  Against the register-staged
+// 4-byte gather it replaces (64 x 64 x 16: a vector load, its bounds test and
+// an LDS write per element) a slot costs one add, the bounds test and the
+// copy.  Bound by the vector instructions beside the MFMAs: 20 x 19 x 26 x 189
+// -> 280, 7x7: 660 against 845 us (78 TFLOP/s); 8 x 57 x 43 x 50 -> 75, 3x3: 38
+// against 45 us.
+template <int BM, int BK, int NW>
+struct DmaConvA1 {
+    typedef DmaOperand<BM, BK, NW, true> Layout;
+    static constexpr int CPR = Layout::CPR, RPS = Layout::RPS, FLOATS = Layout::FLOATS;
+    static constexpr int L = FLOATS / 64 / NW;  // copies per lane per K-block
+    static constexpr int WALKS = NW >= CPR ? 1 : CPR / NW;
+    static_assert(FLOATS % (64 * NW) == 0 && (NW % CPR == 0 || CPR % NW == 0) && RPS * BK == 64, "piece geometry");
+    // byte offset (modulo 2^32: a padded origin lies before its image) and
+    // position of each slot's window origin
+    unsigned org[L];
+    int ih0[L], iw0[L];
+    int col[WALKS], ci[WALKS], kw[WALKS], kh[WALKS];
+    int H, W, Cin, KW;
+    int dkh, dkw, dci;  // one step of the walk
+
+    // blocks: K-blocks from one issue to the next
+    __device__ __forceinline__ void init(const KernelArgs &p, int m0, int kbeg, int wave, int lane, int blocks = 1)
+    {
+        H = p.H; W = p.W; Cin = p.Cin; KW = p.KW;
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            const int m = m0 + (i * NW + wave) * RPS + lane / BK;
+            if (m < p.M) {
+                const int wo = m % p.Wo;
+                const int t = m / p.Wo;
+                const int ho = t % p.Ho;
+                ih0[i] = ho * p.sh - p.pt;
+                iw0[i] = wo * p.sw - p.pl;
+                org[i] = (((unsigned)((t / p.Ho) * H) + (unsigned)ih0[i]) * (unsigned)W + (unsigned)iw0[i]) *
+                         (unsigned)(Cin * 4);
+            } else {
+                ih0[i] = -(1 << 30);  // every tap falls outside the image
+                iw0[i] = 0;
+                org[i] = 0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < WALKS; ++u) {
+            col[u] = 4 * (((lane % BK) / 4) ^ ((u * NW + wave) % CPR)) + lane % 4;
+            const int k = kbeg * BK + col[u];
+            const int tap = k / Cin;
+            ci[u] = k - tap * Cin;
+            kh[u] = tap / KW;
+            kw[u] = tap - kh[u] * KW;
+        }
+        const int step = BK * blocks, taps = step / Cin;
+        dci = step - taps * Cin;
+        dkh = taps / KW;
+        dkw = taps - dkh * KW;
+    }
+    // copy K-block k0 (the one the walks stand at), then step the walks
+    __device__ __forceinline__ void issue(const float *x, int k0, int K, float *tile, int wave)
+    {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, 0x7fffffff, 0x00020000);
+        unsigned kofs[WALKS];
+        bool k_ok[WALKS];
+#pragma unroll
+        for (int u = 0; u < WALKS; ++u) {
+            kofs[u] = (((unsigned)kh[u] * (unsigned)W + (unsigned)kw[u]) * (unsigned)Cin + (unsigned)ci[u]) * 4u;
+            k_ok[u] = k0 + col[u] < K;
+        }
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+            constexpr int UM = WALKS - 1;
+            const int u = i & UM;
+            const bool ok = k_ok[u] && (unsigned)(ih0[i] + kh[u]) < (unsigned)H &&
+                            (unsigned)(iw0[i] + kw[u]) < (unsigned)W;
+            const int o = ok ? (int)(org[i] + kofs[u]) : (int)0x80000000;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs, (__attribute__((address_space(3))) void *)(tile + (i * NW + wave) * 64), 4, o, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < WALKS; ++u) {
+            ci[u] += dci;
+            kw[u] += dkw;
+            kh[u] += dkh;
+            if (ci[u] >= Cin) { ci[u] -= Cin; ++kw[u]; }
+            if (kw[u] >= KW) { kw[u] -= KW; ++kh[u]; }
+        }
+    }
+    __device__ __forceinline__ static void read4(const float *tile, int row, int h, int g, float *v)
+    {
+        Layout::read4(tile, row, h, g, v);
+    }
+};
+
+// The A operand's helper: the gathers, or a dense operand of the layout.
+template <int AMODE, int BM, int BK, int NW, bool UNAL>
+struct DmaASel { typedef DmaOperand<BM, BK, NW, AMODE == A_KCONTIG, UNAL> T; };
+template <int BM, int BK, int NW>
+struct DmaASel<A_CONV, BM, BK, NW, false> { typedef DmaConvA<BM, BK, NW> T; };
+template <int BM, int BK, int NW>
+struct DmaASel<A_CONV, BM, BK, NW, true> { typedef DmaConvA1<BM, BK, NW> T; };
+
 // The contraction (dense operands in any of the four layouts, or the
 // convolution's implicit-GEMM gather) with both operand tiles copied
 // straight into STAGES LDS stages (DmaOperand, DmaConvA): S-1
@@ -779,15 +932,15 @@ struct DmaConvA {
 // compiler memory barrier, and the work-group barrier is issued without
 // __syncthreads()'s fence (which would also wait for the copies in flight
 // for later blocks).  Same MFMA group pipeline as gemm_kernel.
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool BETA>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool BETA,
+          bool UA = false, bool UB = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(OCC, 8)))
 gemm_dma_kernel(KernelArgs p)
 {
     typedef GemmTile<BM, BN, BK, WAVES_M, WAVES_N, A_KCONTIG, false, 4, 4> G;  // MFMA and epilogue only
     constexpr int NW = G::NT / 64;
-    typedef typename std::conditional<AMODE == A_CONV, DmaConvA<BM, BK, NW>,
-                                      DmaOperand<BM, BK, NW, AMODE == A_KCONTIG>>::type OpA;
-    typedef DmaOperand<BN, BK, NW, TB> OpB;
+    typedef typename DmaASel<AMODE, BM, BK, NW, UA>::T OpA;
+    typedef DmaOperand<BN, BK, NW, TB, UB> OpB;
     constexpr int A_ST = OpA::FLOATS, B_ST = OpB::FLOATS;  // floats per stage
     constexpr int LPB = OpA::L + OpB::L;                    // copies per lane per K-block
     static_assert(STAGES >= 2 && STAGES <= 4, "two to four LDS stages");
@@ -1617,15 +1770,14 @@ gemm_streamk_kernel(KernelArgs p)
 // groups take the same number of steps, so the work-group's barriers line
 // up; at the end the partial tiles are added through LDS in group order.
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int KS, int STAGES, int AMODE, bool TB, int OCC,
-          bool BETA>
+          bool BETA, bool UA = false, bool UB = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N * KS) __attribute__((amdgpu_waves_per_eu(OCC, 8)))
 gemm_dma_ksplit_kernel(KernelArgs p)
 {
     typedef GemmTile<BM, BN, BK, WAVES_M, WAVES_N, A_KCONTIG, false, 4, 4> G;  // MFMA and epilogue only
     constexpr int GT = G::NT, NW = GT / 64;  // threads and waves per group
-    typedef typename std::conditional<AMODE == A_CONV, DmaConvA<BM, BK, NW>,
-                                      DmaOperand<BM, BK, NW, AMODE == A_KCONTIG>>::type OpA;
-    typedef DmaOperand<BN, BK, NW, TB> OpB;
+    typedef typename DmaASel<AMODE, BM, BK, NW, UA>::T OpA;
+    typedef DmaOperand<BN, BK, NW, TB, UB> OpB;
     constexpr int A_ST = OpA::FLOATS, B_ST = OpB::FLOATS;
     constexpr int GSTAGES = STAGES * (A_ST + B_ST);  // floats of one group's stages
     constexpr int LPB = OpA::L + OpB::L;
@@ -1663,7 +1815,7 @@ gemm_dma_ksplit_kernel(KernelArgs p)
     OpA oa;
     OpB ob;
     if constexpr (AMODE == A_CONV)
-        oa.init(p, m0, kbeg + grp, wave, lane);  // the gather walks this group's K-blocks, KS apart
+        oa.init(p, m0, kbeg + grp, wave, lane, KS);  // the gather walks this group's K-blocks, KS apart
     else
         oa.init(p.lda, m0, p.M, wave, lane);
     ob.init(p.ldb, n0, p.N, wave, lane);
@@ -1672,7 +1824,7 @@ gemm_dma_ksplit_kernel(KernelArgs p)
         const int k0 = (kbeg + st * KS + grp) * BK;
         float *as = gs + s * (A_ST + B_ST);
         if constexpr (AMODE == A_CONV)
-            oa.issue(p.A, k0, klim, as, wave, KS);
+            oa.issue(p.A, k0, klim, as, wave);
         else
             oa.issue(p.A, p.lda, m0, k0, klim, as, wave);
         ob.issue(p.B, p.ldb, n0, k0, klim, as + A_ST, wave);
@@ -1771,15 +1923,15 @@ gemm_dma_ksplit_kernel(KernelArgs p)
 // there.  The epilogue's stores count on the same vector-memory counter as
 // the copies and retire in order, so a wait issued after them only waits
 // longer, never too little.
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool BETA>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool BETA,
+          bool UA = false, bool UB = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(OCC, 8)))
 gemm_dma_streamk_kernel(KernelArgs p)
 {
     typedef GemmTile<BM, BN, BK, WAVES_M, WAVES_N, A_KCONTIG, false, 4, 4> G;  // MFMA and epilogue only
     constexpr int NT = G::NT, NW = NT / 64;
-    typedef typename std::conditional<AMODE == A_CONV, DmaConvA<BM, BK, NW>,
-                                      DmaOperand<BM, BK, NW, AMODE == A_KCONTIG>>::type OpA;
-    typedef DmaOperand<BN, BK, NW, TB> OpB;
+    typedef typename DmaASel<AMODE, BM, BK, NW, UA>::T OpA;
+    typedef DmaOperand<BN, BK, NW, TB, UB> OpB;
     constexpr int A_ST = OpA::FLOATS, B_ST = OpB::FLOATS;
     constexpr int LPB = OpA::L + OpB::L;
     static_assert(STAGES >= 2 && STAGES <= 4, "two to four LDS stages");
