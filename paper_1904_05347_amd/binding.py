@@ -121,6 +121,31 @@ def load():
     return lib
 
 
+# The native marshalling (csrc/pk_torch.cpp) of the plain tensor calls, bound to
+# the loaded library's entry points at first use.
+EXT_PATH = os.path.join(HERE, "_pk_torch.so")
+_NATIVE_ENTRIES = ("pk_sgemm_ws", "pk_sgemm_workspace_bytes", "pk_conv2d_fwd", "pk_conv2d_workspace_bytes",
+                   "pk_conv2d_out_dims", "pk_conv2d_same_pads", "pk_conv2d_winograd_tile_fwd",
+                   "pk_conv2d_winograd_tile_workspace_bytes")
+_native = None
+
+
+def _load_native():
+    global _native
+    lib = load()
+    if not os.path.exists(EXT_PATH):
+        raise PkLibraryMissing("_pk_torch.so is not built: run `python -m paper_1904_05347_amd.build`")
+    import importlib.machinery
+    import importlib.util
+    import torch  # noqa: F401  (the module links against torch's libraries)
+    loader = importlib.machinery.ExtensionFileLoader("_pk_torch", EXT_PATH)
+    mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_pk_torch", loader))
+    loader.exec_module(mod)
+    mod.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_ENTRIES))
+    _native = mod
+    return mod
+
+
 def _check(status: int, what: str) -> None:
     if status != PK_OK:
         raise PkError(status, what, _lib.pk_last_invalid_param())
@@ -309,6 +334,10 @@ def gemm(a, b, c=None, alpha=1.0, beta=0.0, trans_a=False, trans_b=False, worksp
     ``sgemm_workspace_bytes``); when None, one of the size the library asks
     for is allocated.
     """
+    # the plain case natively (None: anything else, errors included)
+    r = (_native or _load_native()).gemm(a, b, c, alpha, beta, trans_a, trans_b, workspace)
+    if r is not None:
+        return r
     import torch
     _check_f32_cuda(a, "a")
     _check_f32_cuda(b, "b")
@@ -361,6 +390,9 @@ def conv2d_fwd(x, w, stride=(1, 1), padding="SAME", out=None, workspace=None):
     work-groups (split-K or stream-K, see ``conv2d_workspace_bytes``); when
     None, one of the size the chosen configuration needs is allocated.
     """
+    r = (_native or _load_native()).conv2d_fwd(x, w, stride, padding, out, workspace)
+    if r is not None:
+        return r
     import torch
     _check_f32_cuda(x, "x")
     _check_f32_cuda(w, "w")
@@ -402,6 +434,9 @@ def conv2d_winograd(x, w, padding="SAME", out=None, workspace=None, tile=2):
     workspace (float32 device tensor of at least
     ``conv2d_winograd_workspace_bytes(..., tile)`` bytes) is allocated when None.
     """
+    r = (_native or _load_native()).conv2d_winograd(x, w, padding, out, workspace, tile)
+    if r is not None:
+        return r
     import torch
     _check_f32_cuda(x, "x")
     _check_f32_cuda(w, "w")

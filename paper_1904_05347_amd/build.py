@@ -1,7 +1,8 @@
 """Build the HIP library libpk.so for gfx950, in-tree.
 
-Each source under csrc/ is compiled by hipcc in parallel, then linked into a
-shared library next to this file.  Run as ``python -m paper_1904_05347_amd.build``.
+Each .hip source under csrc/ is compiled by hipcc in parallel, then linked into a
+shared library next to this file; csrc/pk_torch.cpp (host code, torch's C++
+headers) becomes the Python module ``_pk_torch`` beside it.  Run as ``python -m paper_1904_05347_amd.build``.
 
 ``python -m paper_1904_05347_amd.build --sanitized`` builds a second copy,
 ``_build_san/libpk_san.so``, whose HOST code (argument checks, shape
@@ -17,6 +18,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -66,11 +68,37 @@ def _compile(src: str, build_dir: str = BUILD, extra=()):
     return obj, remarks
 
 
+EXT = os.path.join(HERE, "_pk_torch.so")
+
+
+def build_ext() -> str:
+    """The native marshalling of the tensor calls, for the torch of this interpreter."""
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    tlib = os.path.join(troot, "lib")
+    tmp = EXT + ".tmp%d" % os.getpid()
+    cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi())]
+           + ["-isystem" + d for d in (os.path.join(troot, "include"),
+                                       os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+                                       os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
+                                       sysconfig.get_paths()["include"])]
+           + [os.path.join(CSRC, "pk_torch.cpp"), "-o", tmp, "-L" + tlib, "-Wl,-rpath," + tlib,
+              "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10_hip", "-lc10"])
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed for pk_torch.cpp:\n" + res.stderr)
+    os.replace(tmp, EXT)
+    return EXT
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(BUILD, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
+        ext = ex.submit(build_ext)
         results = list(ex.map(_compile, srcs))
+        ext.result()
     objs = [o for o, _ in results]
     with open(RESOURCE_LOG, "w") as fh:
         for _, remarks in results:
@@ -80,7 +108,7 @@ def build(verbose: bool = True) -> str:
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB)
     if verbose:
-        print("built", LIB)
+        print("built", LIB, "and", EXT)
     return LIB
 
 
