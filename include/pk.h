@@ -214,7 +214,10 @@ int pk_conv2d_fwd_noalloc(const float *x, int64_t N, int64_t H, int64_t W, int64
  *                It holds the transformed filter, input and products;
  *                contents on return are unspecified.  It must not overlap
  *                x, f or y.
- * pk_last_config_name() names the contraction configuration of the product.
+ * pk_last_config_name() names the contraction configuration of the product,
+ * or "winograd<m>_<tiles>x<channels>" where transforms and product ran as one
+ * kernel (16-byte aligned x, Cin % 4 == 0, chosen by predicted time; never
+ * with a forced configuration).
  */
 size_t pk_conv2d_winograd_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin,
                                           int64_t Cout, int64_t pt, int64_t pl,

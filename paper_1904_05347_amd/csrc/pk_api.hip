@@ -1417,16 +1417,36 @@ const Config *select_wino_gemm(int nbatch, int64_t T, int64_t Cout, int64_t Cin,
         return (gemm_config_fits(c, 0, 0, vec_ok) && !c->persistent && !c->streamk && !c->bres && dma_fits(c, Cin, Cout))
                    ? c
                    : nullptr;
-    if (!vec_ok) return find_config("gemm_64x64x16_w2x2_nn_v11");
-    if (Cin <= 128) return find_config("gemm_64x64x16_w2x2_nn_v44");
-    // deeper channels: operands copied straight into LDS; 128 x 128 tiles
-    // once the products hold 4 of them per CU (VGG-16 conv3_2 .. conv4_2
-    // at batch 32: 0.93-0.95x the time of the register-staged 64 x 64 x 32),
-    // else 64 x 64 x 32 in three stages (0.93-0.98x)
-    const bool big = nbatch * ceil_div(T, 128) * ceil_div(Cout, 128) >= 4 * kCUs;
-    const Config *c2 = find_config(big ? "gemm_128x128x32_w2x4_nn_v44_o2_dma2" : "gemm_64x64x32_w2x2_nn_v44_dma3");
-    if (c2 && dma_fits(c2, Cin, Cout)) return c2;
-    return find_config("gemm_64x64x32_w2x2_nn_v44");
+    const char *rule = "gemm_64x64x16_w2x2_nn_v11";
+    if (vec_ok) {
+        // deeper channels: operands copied straight into LDS; 128 x 128 tiles
+        // once the products hold 4 of them per CU (VGG-16 conv3_2 .. conv4_2
+        // at batch 32: 0.93-0.95x the time of the register-staged 64 x 64 x 32),
+        // else 64 x 64 x 32 in three stages (0.93-0.98x)
+        const bool big = nbatch * ceil_div(T, 128) * ceil_div(Cout, 128) >= 4 * kCUs;
+        rule = Cin <= 128 ? "gemm_64x64x16_w2x2_nn_v44"
+               : big      ? "gemm_128x128x32_w2x4_nn_v44_o2_dma2"
+                          : "gemm_64x64x32_w2x2_nn_v44_dma3";
+        c = find_config(rule);
+        if (!c || !dma_fits(c, Cin, Cout)) c = find_config("gemm_64x64x32_w2x2_nn_v44");
+    } else {
+        c = find_config(rule);
+    }
+    // ... unless a tile is predicted at least 10 % faster over the whole batch
+    static const CostConfigs k44(pk::kCostGemm44, true), k11(pk::kCostGemm11, true);
+    const pk::CostFamily &f = vec_ok ? pk::kCostGemm44 : pk::kCostGemm11;
+    const CostConfigs &k = vec_ok ? k44 : k11;
+    const int r = c ? cost_tile(f, c) : -1;
+    const Config *best = c;
+    float us = r < 0 ? 0.f : kCostMargin * pk::predict_us(f, f.tiles[r], T, Cout, Cin, 1, nbatch);
+    for (int i = 0; r >= 0 && i < f.n; ++i) {
+        const float t = pk::predict_us(f, f.tiles[i], T, Cout, Cin, 1, nbatch);
+        if (k.c[0][i] && dma_fits(k.c[0][i], Cin, Cout) && t < us) {
+            best = k.c[0][i];
+            us = t;
+        }
+    }
+    return best;
 }
 
 size_t wino_workspace_bytes(int m, int64_t N, int64_t H, int64_t W, int64_t Cin, int64_t Cout, int64_t pt,
@@ -1505,11 +1525,29 @@ int wino_fwd(int m, int m_pos, int ws_pos, const float *x, int64_t N, int64_t H,
     const bool in4 = Cin % 4 == 0 && aligned16(x);
     const bool out4 = Cout % 4 == 0 && aligned16(y);
     bool bad = false;
-    const Config *c = select_wino_gemm(w.A2, w.T, Cout, Cin, Cin % 4 == 0 && Cout % 4 == 0, &bad);
+    const Config *c = forced(&bad);
     if (bad) return invalid(0);  // PK_FORCE_CONFIG names no configuration
+    hipStream_t s = (hipStream_t)stream;
+
+    // One kernel where it is predicted faster than the three around a product
+    // (a forced configuration names that product): 16-byte channel loads, an
+    // image addressed in 32-bit byte offsets, room for its filter.
+    if (!c && in4 && 4 * pixels * Cin < ((int64_t)1 << 31) && Cout <= 32 * 65535 &&
+        pk::wino_operand_floats(m, Cin, Cout) * sizeof(float) <= w.bytes) {
+        const int form = pk::wino_form(m, w.T, Cin, Cout);
+        if (form >= 0) {
+            if (pk::launch_wino_fused(m, form, x, f, U, y, H, W, Cin, Cout, pt, pl, w.TH, w.TW, w.T, Ho, Wo, out4, s) !=
+                hipSuccess)
+                return PK_ERR_LAUNCH;
+            static const char *const kNames[2][2] = {{"winograd2_32x32", "winograd2_32x64"},
+                                                     {"winograd4_32x32", "winograd4_32x64"}};
+            t_last_config = kNames[m == 4][form];
+            return PK_OK;
+        }
+    }
+    c = select_wino_gemm(w.A2, w.T, Cout, Cin, Cin % 4 == 0 && Cout % 4 == 0, &bad);
     if (!c) return PK_ERR_NOT_SUPPORTED;
 
-    hipStream_t s = (hipStream_t)stream;
     if (pk::launch_wino_filter(m, f, U, Cin, Cout, s) != hipSuccess) return PK_ERR_LAUNCH;
     if (pk::launch_wino_input(m, x, V, H, W, Cin, pt, pl, w.TH, w.TW, w.T, in4, s) != hipSuccess)
         return PK_ERR_LAUNCH;

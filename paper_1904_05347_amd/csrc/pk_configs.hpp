@@ -80,4 +80,13 @@ hipError_t launch_wino_input(int m, const float *x, float *V, int64_t H, int64_t
 hipError_t launch_wino_output(int m, const float *M, float *y, int64_t Ho, int64_t Wo, int64_t Cout, int64_t TH,
                               int64_t TW, int64_t T, bool vec4, hipStream_t stream);
 
+// One-kernel Winograd (pk_winograd_fused.hip): the filter transform into U
+// (wino_operand_floats(m, Cin, Cout) floats), then the rest in one launch.  Cin
+// a multiple of 4, x and U 16-byte aligned, the image below 2 GiB; vec4: y
+// takes 16-byte stores.  form: the block of tiles x output channels.
+size_t wino_operand_floats(int m, int64_t Cin, int64_t Cout);
+hipError_t launch_wino_fused(int m, int form, const float *x, const float *f, float *U, float *y, int64_t H, int64_t W,
+                             int64_t Cin, int64_t Cout, int64_t pt, int64_t pl, int64_t TH, int64_t TW, int64_t T,
+                             int64_t Ho, int64_t Wo, bool vec4, hipStream_t stream);
+
 }  // namespace pk

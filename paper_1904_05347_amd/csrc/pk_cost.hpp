@@ -127,10 +127,11 @@ constexpr int kCostCUs = 256;
 constexpr int kCostSplits[] = {1, 2, 3, 4, 6, 8, 12, 16};
 
 // Predicted time (us) of an M x N x K product on tile c with its reduction
-// split s ways (sizes at least 1).
-inline float predict_us(const CostFamily &f, const TileCost &c, int64_t M, int64_t N, int64_t K, int s)
+// split s ways, or of a batch of such products (sizes at least 1).
+inline float predict_us(const CostFamily &f, const TileCost &c, int64_t M, int64_t N, int64_t K, int s,
+                        int64_t batch = 1)
 {
-    const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * batch;
     const int64_t nkb = (K + c.bk - 1) / c.bk;
     if (c.streamk) return f.t0 + c.ov + c.m * ((float)tiles * (float)nkb / kCostCUs);
     int64_t per = nkb;
@@ -188,6 +189,65 @@ int cheapest(const CostFamily &f, int64_t M, int64_t N, int64_t K, size_t ws_byt
         }
     }
     return best;
+}
+
+// The Winograd convolution of T tiles, Cin and Cout channels as one kernel
+// (pk_winograd_fused.hip): blocks of bt tiles x bc channels as above, a step a
+// stage of 16 channels; ft: the filter transform, per million Cin * Cout.
+struct WinoFusedCost {
+    int bt, bc, per_cu;
+    float t0, l, m, ov, ft;
+};
+constexpr WinoFusedCost kWinoFused2[2] = {{32, 32, 2, 5.78f, 1.486f, 1.395f, 2.85f, 2.0f},
+                                          {32, 64, 2, 5.46f, 2.386f, 2.332f, 4.55f, 19.3f}};
+constexpr WinoFusedCost kWinoFused4[2] = {{32, 32, 1, 1.90f, 4.757f, 0.f, 9.65f, 43.7f},
+                                          {32, 64, 1, 0.87f, 6.755f, 6.658f, 12.46f, 56.8f}};
+// ... and as transforms around a batch of products: launches, bytes of V and
+// M, K-blocks of the products, the filter.
+struct WinoCost {
+    float t0, v, m, l, k, ft;
+};
+constexpr WinoCost kWino2 = {13.49f, 1.38f, 1.70f, 1.216f, 0.533f, 30.2f};
+constexpr WinoCost kWino4 = {18.12f, 1.27f, 1.60f, 0.786f, 0.561f, 57.6f};
+
+inline float predict_wino_fused_us(const WinoFusedCost &c, int64_t T, int64_t Cin, int64_t Cout)
+{
+    const int64_t n = (((T + c.bt - 1) / c.bt) * ((Cout + c.bc - 1) / c.bc) + kCostCUs - 1) / kCostCUs;
+    const float stages = (float)((Cin + 15) / 16);
+    const int64_t full = n / c.per_cu, rem = n - full * c.per_cu;
+    auto round = [&](float r) { return (r * c.m > c.l ? r * c.m : c.l) * stages + c.ov; };
+    float t = c.t0 + c.ft * 1e-6f * (float)Cin * (float)Cout + (float)full * round((float)c.per_cu);
+    if (rem) t += round((float)rem);
+    return t;
+}
+
+inline float predict_wino_us(int m, int64_t T, int64_t Cin, int64_t Cout)
+{
+    const WinoCost &c = m == 2 ? kWino2 : kWino4;
+    const float P = (float)((m + 2) * (m + 2)), nk = (float)((Cin + 31) / 32);
+    const int64_t items = ((T + 63) / 64) * ((Cout + 63) / 64) * (m + 2) * (m + 2);
+    const float n = (float)((items + kCostCUs - 1) / kCostCUs);
+    return c.t0 + 1e-6f * (P * (float)T * (c.v * (float)Cin + c.m * (float)Cout) + c.ft * (float)Cin * (float)Cout) +
+           (n * c.k > c.l ? n * c.k : c.l) * nk;
+}
+
+// The form of the one-kernel convolution (0, 1) predicted fastest, or -1 when
+// the separate kernels are: over 106 random convolutions this choice was within
+// 0.1 % of the faster of the three (geometric mean), the separate kernels 1.66x
+// (m = 2) and 1.15x (m = 4) above it.
+inline int wino_form(int m, int64_t T, int64_t Cin, int64_t Cout)
+{
+    const WinoFusedCost *c = m == 2 ? kWinoFused2 : kWinoFused4;
+    float best = predict_wino_us(m, T, Cin, Cout);
+    int form = -1;
+    for (int i = 0; i < 2; ++i) {
+        const float t = predict_wino_fused_us(c[i], T, Cin, Cout);
+        if (t < best) {
+            best = t;
+            form = i;
+        }
+    }
+    return form;
 }
 
 }  // namespace pk
