@@ -20,7 +20,7 @@ CASES = [
     (2, (5, 13, 7, 4, 33, (0, 2, 1, 0)), "winograd2_32x32"),
     (2, (3, 16, 18, 52, 65, (0, 0, 0, 0)), "winograd2_32x32"),
     (2, (1, 249, 250, 12, 61, (1, 1, 1, 1)), "winograd2_32x64"),
-    (4, (3, 43, 39, 20, 43, (1, 1, 1, 1)), "winograd4_32x32"),
+    (4, (3, 43, 39, 12, 43, (1, 1, 1, 1)), "winograd4_32x32"),
     (4, (2, 230, 227, 16, 61, (2, 1, 0, 1)), "winograd4_32x64"),
 ]
 
