@@ -104,6 +104,29 @@ def test_conv_unaligned_configs(geom):
     assert ran >= 14
 
 
+def test_conv_unaligned_infinities_stay_in_their_windows():
+    """An infinity or NaN in the image reaches exactly the outputs whose window
+    holds it."""
+    torch, pk = require_gpu()
+    rng = np.random.default_rng(3)
+    N, H, W, Cin, Cout = 2, 9, 10, 5, 7
+    f = np.abs(wl.uniform(rng, 9 * Cin * Cout)).reshape(3, 3, Cin, Cout) + np.float32(0.5)
+    for value in (np.inf, np.nan):
+        for n, h, w, c in [(0, 4, 5, 0), (1, 8, 9, 4), (1, 0, 0, 2), (0, 3, 9, 1)]:
+            x = np.zeros((N, H, W, Cin), np.float32)
+            x[n, h, w, c] = value
+            hit = np.zeros((N, H, W), bool)
+            hit[n, max(0, h - 1):h + 2, max(0, w - 1):w + 2] = True
+            for name in [q for q in _unaligned(pk, 1) if "_v11" in q]:
+                pk.force_config(name)
+                try:
+                    y = host(pk.conv2d_fwd(dev(x), dev(f)))
+                finally:
+                    pk.force_config(None)
+                assert np.array_equal(~np.isfinite(y).all(axis=-1), hit), (name, value, n, h, w, c)
+                assert np.all(y[~hit] == 0), (name, value)
+
+
 def test_narrow_tile_swizzle_and_tt():
     """The 32- and 96-column tiles (k rows swapped in pairs) and the TT forms
     on aligned operands, several K-blocks deep, every column distinct."""
