@@ -141,7 +141,7 @@ def _load_native():
     loader = importlib.machinery.ExtensionFileLoader("_pk_torch", EXT_PATH)
     mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_pk_torch", loader))
     loader.exec_module(mod)
-    mod.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_ENTRIES))
+    mod.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_ENTRIES), _check)
     _native = mod
     return mod
 

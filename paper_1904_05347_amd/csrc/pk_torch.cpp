@@ -10,9 +10,11 @@
 //
 // Each function answers None whenever a call is anything but the plain case
 // (a tensor subclass, an active torch mode, another type, device, layout or
-// argument form, a shape that does not match, a C-ABI status other than PK_OK):
-// binding.py then runs its own checks and the same C-ABI call, so errors and
-// unusual forms behave as they always did.  Nothing is kept between calls.
+// argument form, a shape that does not match, a C-ABI status that refuses the
+// call): binding.py then runs its own checks and the same C-ABI call, so errors
+// and unusual forms behave as they always did.  A failed launch is raised here:
+// what went before it on the stream must not run twice.  Nothing is kept
+// between calls.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -39,6 +41,14 @@ decltype(&pk_conv2d_out_dims) f_out_dims;
 decltype(&pk_conv2d_same_pads) f_same_pads;
 decltype(&pk_conv2d_winograd_tile_fwd) f_winograd;
 decltype(&pk_conv2d_winograd_tile_workspace_bytes) f_winograd_workspace_bytes;
+PyObject *f_check;  // binding._check(status, entry point): raises
+
+// The answer to a status other than PK_OK.
+PyObject *refused(int st, const char *entry)
+{
+    if (st != PK_ERR_LAUNCH) Py_RETURN_NONE;
+    return PyObject_CallFunction(f_check, "is", st, entry);
+}
 
 // A plain fp32 tensor on a GPU, or NULL.
 const at::Tensor *plain(PyObject *o)
@@ -71,8 +81,9 @@ bool as_int(PyObject *o, int64_t *v)
 bool as_float(PyObject *o, float *v)
 {
     if (PyFloat_CheckExact(o)) {
-        *v = (float)PyFloat_AS_DOUBLE(o);
-        return true;
+        const double d = PyFloat_AS_DOUBLE(o);
+        *v = (float)d;
+        return *v != 0.f || d == 0.0;  // a beta that underflows isn't "no beta"
     }
     int64_t i;
     if (!as_int(o, &i) || i < -(1 << 24) || i > (1 << 24)) return false;
@@ -142,7 +153,7 @@ PyObject *py_gemm(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     Py_BEGIN_ALLOW_THREADS
     st = f_sgemm_ws(fa, fb, M, N, K, alpha, pa, lda, pb, ldb, beta, pc, ldc, ws, ws_bytes, stream);
     Py_END_ALLOW_THREADS
-    if (st != PK_OK) Py_RETURN_NONE;
+    if (st != PK_OK) return refused(st, "pk_sgemm_ws");
     if (fresh) return THPVariable_Wrap(std::move(c));
     Py_INCREF(args[2]);
     return args[2];
@@ -242,7 +253,7 @@ PyObject *py_conv2d_fwd(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     st = f_conv2d_fwd(px, g.N, g.H, g.W, g.Cin, pw, g.KH, g.KW, g.Cout, g.sh, g.sw, g.p[0], g.p[1], g.p[2], g.p[3],
                       py, g.Ho, g.Wo, ws, ws_bytes, stream);
     Py_END_ALLOW_THREADS
-    if (st != PK_OK) Py_RETURN_NONE;
+    if (st != PK_OK) return refused(st, "pk_conv2d_fwd");
     return answer(args[4], std::move(y));
     END_HANDLE_TH_ERRORS
 }
@@ -273,16 +284,17 @@ PyObject *py_conv2d_winograd(PyObject *, PyObject *const *args, Py_ssize_t nargs
     st = f_winograd(px, g.N, g.H, g.W, g.Cin, pw, g.KH, g.KW, g.Cout, 1, 1, g.p[0], g.p[1], g.p[2], g.p[3], py, g.Ho,
                     g.Wo, m, ws, ws_bytes, stream);
     Py_END_ALLOW_THREADS
-    if (st != PK_OK) Py_RETURN_NONE;
+    if (st != PK_OK) return refused(st, "pk_conv2d_winograd_tile_fwd");
     return answer(args[3], std::move(y));
     END_HANDLE_TH_ERRORS
 }
 
-// bind(addresses): the eight entry points above, in their order.
+// bind(addresses, check): the eight entry points above, in their order, and the
+// function that raises for a status.
 PyObject *py_bind(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    if (nargs != 8) {
-        PyErr_SetString(PyExc_TypeError, "bind takes the addresses of eight entry points");
+    if (nargs != 9) {
+        PyErr_SetString(PyExc_TypeError, "bind takes the addresses of eight entry points and a function");
         return nullptr;
     }
     void *p[8];
@@ -301,6 +313,8 @@ PyObject *py_bind(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     f_same_pads = (decltype(f_same_pads))p[5];
     f_winograd = (decltype(f_winograd))p[6];
     f_winograd_workspace_bytes = (decltype(f_winograd_workspace_bytes))p[7];
+    Py_INCREF(args[8]);
+    Py_XSETREF(f_check, args[8]);
     Py_RETURN_NONE;
 }
 

@@ -75,7 +75,7 @@ def test_native_calls_decline_and_raise_as_before(monkeypatch):
     x, w = torch.ones(1, 5, 5, 4, device="cuda"), torch.ones(3, 3, 4, 4, device="cuda")
     bad = [
         lambda: pk.gemm(a.double(), a), lambda: pk.gemm(a.cpu(), a), lambda: pk.gemm(a, a[:4]),
-        lambda: pk.gemm(a, a, beta=1.0), lambda: pk.gemm(a, a, torch.ones(4, 8, device="cuda")),
+        lambda: pk.gemm(a, a, beta=1.0), lambda: pk.gemm(a, a, beta=1e-50), lambda: pk.gemm(a, a, torch.ones(4, 8, device="cuda")),
         lambda: pk.gemm(a.t()[:, :4], a), lambda: pk.gemm(a, a, a), lambda: pk.conv2d_fwd(x[0], w),
         lambda: pk.conv2d_fwd(x, w[:, :, :3]), lambda: pk.conv2d_fwd(x, w, padding="WIDE"),
         lambda: pk.conv2d_fwd(x, w, stride=0), lambda: pk.conv2d_fwd(x, w, out=x),
@@ -126,3 +126,32 @@ def test_native_call_runs_on_the_current_stream():
         g.replay()
         torch.cuda.synchronize()
         assert bool((c == 512).all())
+
+
+def test_native_call_raises_a_failed_launch_once():
+    """A launch the runtime refuses is reported, not tried again: with beta, what
+    ran before it would run twice."""
+    import ctypes
+
+    torch, pk = require_gpu()
+    from paper_1904_05347_amd import binding
+    native = binding._native or binding._load_native()
+    lib = binding.load()
+    addresses = [ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in binding._NATIVE_ENTRIES]
+    calls = []
+    i64, f32, ptr, ch = ctypes.c_int64, ctypes.c_float, ctypes.c_void_p, ctypes.c_char
+
+    @ctypes.CFUNCTYPE(ctypes.c_int, ch, ch, i64, i64, i64, f32, ptr, i64, ptr, i64, f32, ptr, i64, ptr,
+                      ctypes.c_size_t, ptr)
+    def refuses(*args):
+        calls.append(args)
+        return binding.PK_ERR_LAUNCH
+
+    a, c = torch.ones(8, 8, device="cuda"), torch.ones(8, 8, device="cuda")
+    native.bind(ctypes.cast(refuses, ctypes.c_void_p).value, *addresses[1:], binding._check)
+    try:
+        with pytest.raises(pk.PkError) as e:
+            pk.gemm(a, a, c, beta=1.0)
+    finally:
+        native.bind(*addresses, binding._check)
+    assert e.value.status == binding.PK_ERR_LAUNCH and len(calls) == 1 and bool((c == 1).all())
