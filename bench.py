@@ -79,7 +79,7 @@ def kernel_source_hash():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_1904_05347_amd", "csrc")
-    skip = {"pk_winograd.hip", "pk_probe.hip"}
+    skip = {"pk_winograd.hip", "pk_winograd.hpp", "pk_winograd_fused.hip", "pk_probe.hip"}
     for path in sorted(glob.glob(os.path.join(csrc, "*.hip")) + glob.glob(os.path.join(csrc, "*.hpp"))):
         if os.path.basename(path) in skip:
             continue
