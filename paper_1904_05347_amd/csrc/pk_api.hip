@@ -424,6 +424,36 @@ static_assert(kMemo == 1 << (64 - 58), "a slot per value of the hash's top bits"
 // be predicted to take its place: the prediction's own error (6-10 % rms).
 constexpr float kCostMargin = 0.9f;
 
+// The tile (cfgs: the family's configurations) and split of the least predicted
+// time among the usable ones, or the rule's configuration.  want: the rule's
+// split; rs: that split as far as the workspace holds it.  Chains and the
+// margin are judged by `want` also where only rs fits: a call whose workspace
+// is just what the query for it asked must choose what the query chose (by rs,
+// one convolution in a hundred fell back to a slower choice, half of these
+// with a longer chain).  Only where no tile has such a chain is rs the measure.
+template <typename F>
+const Config *choose(const pk::CostFamily &f, const Config *const *cfgs, const Config *rule, int64_t M, int64_t N,
+                     int64_t K, size_t ws_bytes, int want, int rs, F usable, int *splits)
+{
+    int s = 1;
+    float us = 0.f;
+    int i = pk::cheapest(f, M, N, K, ws_bytes, pk::chain_of(K, rule->kgroups, want), usable, &s, &us);
+    if (i < 0 && rs < want) {
+        i = pk::cheapest(f, M, N, K, ws_bytes, pk::chain_of(K, rule->kgroups, rs), usable, &s, &us);
+        want = rs;
+    }
+    const int r = cost_tile(f, rule);
+    auto beats_rule = [&](int split) {
+        return r < 0 || us <= kCostMargin * pk::predict_us(f, f.tiles[r], M, N, K, split);
+    };
+    if (i < 0 || !(beats_rule(want) || beats_rule(rs))) {
+        *splits = rs;
+        return rule;
+    }
+    *splits = s;
+    return cfgs[i];
+}
+
 // Products that no table entry serves: rules measured shape by shape, whose
 // choice stands unless pk_cost.hpp predicts a better one (select_gemm):
 //   - K <= 64: 64 x 64 tiles; for NN products with K == 64 and N a multiple
@@ -509,20 +539,10 @@ const Config *predict_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int6
     *splits = 1;
     const Config *rule = select_gemm_rule(ta, tb, M, N, K, lda, ldb, ldc, vec_ok);
     if (!rule || rule->bres) return rule;
-    int rs = gemm_splits(rule, M, N, K);
-    if (rs > 1 && ws_bytes < (size_t)rs * (size_t)M * (size_t)N * sizeof(float)) rs = 1;
-    int s = 1;
-    float us = 0.f;
-    const int i = pk::cheapest(
-        f, M, N, K, ws_bytes, pk::chain_of(K, rule->kgroups, rs),
-        [&](int t) { return k.c[l][t] && dma_fits(k.c[l][t], lda, ldb); }, &s, &us);
-    const int r = cost_tile(f, rule);
-    if (i < 0 || (r >= 0 && us > kCostMargin * pk::predict_us(f, f.tiles[r], M, N, K, rs))) {
-        *splits = rs;
-        return rule;
-    }
-    *splits = s;
-    return k.c[l][i];
+    const int want = gemm_splits(rule, M, N, K);
+    const bool room = want <= 1 || ws_bytes >= (size_t)want * (size_t)M * (size_t)N * sizeof(float);
+    return choose(f, k.c[l], rule, M, N, K, ws_bytes, want, room ? want : 1,
+                  [&](int t) { return k.c[l][t] && dma_fits(k.c[l][t], lda, ldb); }, splits);
 }
 
 const Config *select_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
@@ -609,21 +629,10 @@ const Config *predict_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb
     *splits = 1;
     const Config *rule = select_conv_rule(M, Cout, K, va4, vb4, dma_ok, allow_sk);
     if (!rule) return nullptr;
-    int rs = rule->streamk ? 1 : choose_splits(rule, M, Cout, K);
-    if (rs > 1 && ws_bytes < (size_t)rs * (size_t)M * (size_t)Cout * sizeof(float)) rs = 1;
-    int s = 1;
-    float us = 0.f;
-    const int i = !dma_ok ? -1
-                          : pk::cheapest(
-                                f, M, Cout, K, ws_bytes, pk::chain_of(K, rule->kgroups, rs),
-                                [&](int t) { return k.c[0][t] && (allow_sk || !f.tiles[t].streamk); }, &s, &us);
-    const int r = cost_tile(f, rule);
-    if (i < 0 || (r >= 0 && us > kCostMargin * pk::predict_us(f, f.tiles[r], M, Cout, K, rs))) {
-        *splits = rs;
-        return rule;
-    }
-    *splits = s;
-    return k.c[0][i];
+    const int want = rule->streamk ? 1 : choose_splits(rule, M, Cout, K);
+    const bool room = want <= 1 || ws_bytes >= (size_t)want * (size_t)M * (size_t)Cout * sizeof(float);
+    return choose(f, k.c[0], rule, M, Cout, K, ws_bytes, want, room ? want : 1,
+                  [&](int t) { return dma_ok && k.c[0][t] && (allow_sk || !f.tiles[t].streamk); }, splits);
 }
 
 const Config *select_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool dma_ok, bool allow_sk,
