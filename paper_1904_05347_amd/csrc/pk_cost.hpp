@@ -234,10 +234,18 @@ inline float predict_wino_us(int m, int64_t T, int64_t Cin, int64_t Cout)
 // the separate kernels are: over 106 random convolutions this choice was within
 // 0.1 % of the faster of the three (geometric mean), the separate kernels 1.66x
 // (m = 2) and 1.15x (m = 4) above it.
+// Near the line the predictions err by up to a quarter where channels are deep
+// (a stage's latency counts for more): of 110 convolutions measured, most of
+// them near it, every one slower as one kernel had more than 100 channels and a
+// predicted ratio of 0.87 or more (4 x 31 x 31 x 104 -> 644, m = 4: 48.7 against
+// 40.6 us; 2 x 64 x 64 x 424 -> 24, m = 2: 56.8 against 44.1), while up to 100
+// channels the one kernel gained 2 to 36 % there.  So deeper ones need 0.85.
+constexpr int64_t kWinoDeep = 100;
+constexpr float kWinoDeepMargin = 0.85f;
 inline int wino_form(int m, int64_t T, int64_t Cin, int64_t Cout)
 {
     const WinoFusedCost *c = m == 2 ? kWinoFused2 : kWinoFused4;
-    float best = predict_wino_us(m, T, Cin, Cout);
+    float best = (Cin > kWinoDeep ? kWinoDeepMargin : 1.f) * predict_wino_us(m, T, Cin, Cout);
     int form = -1;
     for (int i = 0; i < 2; ++i) {
         const float t = predict_wino_fused_us(c[i], T, Cin, Cout);
