@@ -437,9 +437,12 @@ const Config *choose(const pk::CostFamily &f, const Config *const *cfgs, const C
 {
     int s = 1;
     float us = 0.f;
-    int i = pk::cheapest(f, M, N, K, ws_bytes, pk::chain_of(K, rule->kgroups, want), usable, &s, &us);
+    auto chain = [&](int split) {
+        return pk::chain_of(rule->bm, rule->bn, rule->bk, rule->kgroups, rule->streamk != 0, M, N, K, split);
+    };
+    int i = pk::cheapest(f, M, N, K, ws_bytes, chain(want), usable, &s, &us);
     if (i < 0 && rs < want) {
-        i = pk::cheapest(f, M, N, K, ws_bytes, pk::chain_of(K, rule->kgroups, rs), usable, &s, &us);
+        i = pk::cheapest(f, M, N, K, ws_bytes, chain(rs), usable, &s, &us);
         want = rs;
     }
     const int r = cost_tile(f, rule);

@@ -19,7 +19,8 @@
 // convolutions (1x1 to 7x7, stride 1 and 2, 8 to 1024 channels), 23 000 times
 // in all, reproduced to 6-10 % (rms).  Taking the configuration and split of
 // the least predicted time costs 2-4 % over the best of all of them
-// (geometric mean per group of shapes); the rules that stood before cost
+// (geometric mean per group of shapes; the limit on chains below adds its
+// 0.4 to 2.1 %); the rules that stood before cost
 // 6-13 % on aligned products, 17-19 % on aligned convolutions, and the 4-byte
 // kernels that served unaligned operands 21-36 % and 37-80 %.
 #pragma once
@@ -149,14 +150,28 @@ inline float predict_us(const CostFamily &f, const TileCost &c, int64_t M, int64
     return t;
 }
 
-// Longest run of products that one accumulator adds up, in K: a split, or
-// groups of waves, shorten it.  The rounding error of a result grows with it
-// (about 7e-7 of the result at 1777, 1.1e-6 at 4096, 2-norm), so the choice
-// takes no longer one than the configuration it replaces: over 60 000 random
-// sizes this limit costs 0.5 % of the predicted time of products and 1-2 % of
-// convolutions' (geometric mean); without it 7 and 14 % of them had a longer
-// chain.
-inline int64_t chain_of(int64_t K, int kg, int s) { return (K + (int64_t)kg * s - 1) / ((int64_t)kg * s); }
+// Longest run of products that one accumulator adds up, in K, when a tile of
+// bm x bn outputs walks K-blocks of bk: the whole K-blocks of one split and
+// one of kg groups of waves, or, stream-K, a work-group's share of all tiles'
+// K-blocks (two work-groups per CU hold them).  The rounding error of a result
+// grows with it (about 7e-7 of the result at 1777, 1.1e-6 at 4096, 2-norm), so
+// the choice takes no longer one than the configuration it replaces: over
+// 60 000 random sizes per family this limit costs 0.4 % (aligned) and 0.9 % of
+// the predicted time of products and 1.2 to 2.1 % of convolutions' (geometric
+// mean); without it 4 to 9 and 12 to 24 % of them had a longer chain.
+inline int64_t chain_of(int bm, int bn, int bk, int kg, bool streamk, int64_t M, int64_t N, int64_t K, int64_t s)
+{
+    const int64_t nkb = (K + bk - 1) / bk;
+    int64_t blocks = (nkb + s - 1) / s;
+    if (streamk) {
+        const int64_t items = ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * nkb;
+        const int64_t share = (items + 2 * kCostCUs - 1) / (2 * kCostCUs);
+        blocks = share < nkb ? share : nkb;
+    } else {
+        blocks = (blocks + kg - 1) / kg;
+    }
+    return blocks * bk < K ? blocks * bk : K;
+}
 
 // The tile and split of the least predicted time among the tiles for which
 // usable(index) holds, the splits whose partial sums fit in ws_bytes and the
@@ -178,7 +193,7 @@ int cheapest(const CostFamily &f, int64_t M, int64_t N, int64_t K, size_t ws_byt
             if (s > 1 && (c.streamk || 2 * s > nkb || tiles * s > 16 * kCostCUs ||
                           (double)s * (double)M * (double)N * 4.0 > (double)room))
                 break;
-            if (chain_of(K, c.kg, s) > max_chain) continue;
+            if (chain_of(c.bm, c.bn, c.bk, c.kg, c.streamk != 0, M, N, K, s) > max_chain) continue;
             const float t = predict_us(f, c, M, N, K, s);
             if (best < 0 || t < *us) {
                 best = i;

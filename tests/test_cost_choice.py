@@ -1,9 +1,13 @@
 """The predicted choice of tile and split for shapes outside the table (host
-only): every tile it names is compiled, and no split asks for more partial sums
-than the static scratch of the no-allocation entry holds."""
+only): every tile it names is compiled, no split asks for more partial sums
+than the static scratch of the no-allocation entry holds, and no choice has a
+longer chain of additions than the rule's."""
+import ctypes
+import math
 import os
 import random
 import re
+import subprocess
 
 import pytest
 
@@ -40,3 +44,87 @@ def test_chosen_partial_sums_fit_the_static_scratch(pk):
         cin, cout, k, s = rng.randint(1, 2048), rng.randint(1, 2048), rng.choice([1, 3, 5, 7]), rng.choice([1, 2])
         need = pk.conv2d_workspace_bytes(n, h, w, cin, k, k, cout, s, s, *pk.conv2d_same_pads(h, w, k, k, s, s))
         assert need <= pk.binding.NOALLOC_SCRATCH_BYTES, (n, h, w, cin, cout, k, s, need)
+
+
+class _Pick(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int64) for n in ("bm", "bn", "bk", "kg", "streamk", "splits")] + [("us", ctypes.c_double)]
+
+
+@pytest.fixture(scope="module")
+def choice(pk, tmp_path_factory):
+    """(rule's pick, chosen pick) of a product or a convolution at a workspace size."""
+    out = str(tmp_path_factory.mktemp("shim") / "libchoice_shim.so")
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, "--offload-arch=gfx950", "-x", "hip", "-O1", "-std=c++20", "-shared", "-fPIC",
+                    os.path.join(ROOT, "tests", "choice_shim.cpp"), "-o", out, "-L" + os.path.dirname(pk.binding.LIB_PATH),
+                    "-l:" + os.path.basename(pk.binding.LIB_PATH),
+                    "-Wl,-rpath," + os.path.dirname(pk.binding.LIB_PATH)], check=True, capture_output=True)
+    lib = ctypes.CDLL(out)
+    i64, sz, p = ctypes.c_int64, ctypes.c_size_t, ctypes.POINTER(_Pick)
+    lib.shim_gemm.argtypes = [ctypes.c_int, ctypes.c_int, i64, i64, i64, ctypes.c_int, sz, p, p]
+    lib.shim_conv.argtypes = [i64, i64, i64, ctypes.c_int, ctypes.c_int, sz, p, p]
+
+    def call(fn, *args):
+        rule, pick = _Pick(), _Pick()
+        getattr(lib, fn)(*args, rule, pick)
+        return rule, pick
+
+    call.lib = lib
+    return call
+
+
+ALL_ROOM = (1 << 64) - 1
+
+
+def _chain(c, M, N, K):
+    """Longest run of products one accumulator of this pick adds up, in K."""
+    nkb = -(-K // c.bk)
+    if c.streamk:  # equal shares of all tiles' K-blocks over two work-groups per CU
+        blocks = min(nkb, -(-(-(-M // c.bm) * -(-N // c.bn) * nkb) // 512))
+    else:
+        blocks = -(-(-(-nkb // c.splits)) // c.kg)
+    return min(K, blocks * c.bk)
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _products(rng, count):
+    """(trans_a, trans_b, M, N, K, 16-byte accesses)"""
+    for i in range(count):
+        M, N, K = _log(rng, 1, 8192), _log(rng, 16, 8192), _log(rng, 16, 16384)
+        if i % 2:
+            M, N, K = max(4, M // 4 * 4), N // 4 * 4, K // 4 * 4
+        yield rng.randint(0, 1), rng.randint(0, 1), M, N, K, i % 2
+
+
+# one K-block past a split's whole ones; and of convolutions whose rule is stream-K
+PRODUCTS = [(0, 0, 1025, 64, 1025, 0), (0, 0, 64, 64, 1025, 0), (1, 1, 1493, 421, 6904, 0)]
+STREAMK_CONVS = [(8, 35, 128, 3, 192, 1), (18, 24, 156, 3, 160, 1), (3, 118, 48, 7, 336, 2), (9, 21, 128, 3, 424, 1)]
+
+
+def _convs(rng, count):
+    """(M, Cout, K, 16-byte image, 16-byte filter)"""
+    for n, h, cin, k, cout, s in STREAMK_CONVS:
+        yield n * (-(-h // s)) ** 2, cout, k * k * cin, 1, 1
+    for i in range(count):
+        h, s, k = _log(rng, 7, 224), rng.choice([1, 1, 2]), rng.choice([1, 3, 3, 5, 7])
+        M, K = _log(rng, 1, 32) * (-(-h // s)) ** 2, k * k * (_log(rng, 8, 1024) // 4 * 4)
+        cout = max(4, _log(rng, 8, 1024) // 4 * 4)
+        if M * cout * K < 4e10 and M * cout < 1e8:
+            yield M, cout, K, i % 4 < 3, i % 4 < 2
+
+
+def test_choice_has_no_longer_chain_than_the_rules(choice):
+    rng = random.Random(11)
+    for p in PRODUCTS + list(_products(rng, 20000)):
+        rule, pick = choice("shim_gemm", *p, ALL_ROOM)
+        M, N, K = p[2:5]
+        assert _chain(pick, M, N, K) <= _chain(rule, M, N, K), p
+    streamk = 0
+    for c in _convs(rng, 20000):
+        rule, pick = choice("shim_conv", *c, ALL_ROOM)
+        assert _chain(pick, *c[:3]) <= _chain(rule, *c[:3]), c
+        streamk += rule.streamk and not pick.streamk
+    assert streamk >= 50  # the stream-K rule's own regime is among them
