@@ -363,6 +363,12 @@ bool dma_fits(const Config *c, int64_t lda, int64_t ldb)
 
 int gemm_splits(const Config *c, int64_t M, int64_t N, int64_t K);
 
+// Whether ws_bytes hold the partial sums of a split (one needs none).
+bool splits_fit(int splits, int64_t M, int64_t N, size_t ws_bytes)
+{
+    return splits <= 1 || ws_bytes >= (size_t)splits * (size_t)M * (size_t)N * sizeof(float);
+}
+
 // The configurations of a cost family's tiles, looked up once: one row per
 // GEMM layout (NN, NT, TN, TT), the first row for convolutions; NULL where a
 // layout has no such form.
@@ -425,32 +431,25 @@ static_assert(kMemo == 1 << (64 - 58), "a slot per value of the hash's top bits"
 constexpr float kCostMargin = 0.9f;
 
 // The tile (cfgs: the family's configurations) and split of the least predicted
-// time among the usable ones, or the rule's configuration.  want: the rule's
-// split; rs: that split as far as the workspace holds it.  Chains and the
-// margin are judged by `want` also where only rs fits: a call whose workspace
-// is just what the query for it asked must choose what the query chose (by rs,
-// one convolution in a hundred fell back to a slower choice, half of these
-// with a longer chain).  Only where no tile has such a chain is rs the measure.
+// time among the usable ones whose partial sums fit in ws_bytes, or the rule's
+// configuration at its split.  A choice that asks for less workspace than the
+// rule's also has to beat what the rules run without one: `bare`, unsplit.
 template <typename F>
-const Config *choose(const pk::CostFamily &f, const Config *const *cfgs, const Config *rule, int64_t M, int64_t N,
-                     int64_t K, size_t ws_bytes, int want, int rs, F usable, int *splits)
+const Config *choose(const pk::CostFamily &f, const Config *const *cfgs, const Config *rule, const Config *bare,
+                     int64_t M, int64_t N, int64_t K, size_t ws_bytes, int rule_splits, F usable, int *splits)
 {
     int s = 1;
     float us = 0.f;
-    auto chain = [&](int split) {
-        return pk::chain_of(rule->bm, rule->bn, rule->bk, rule->kgroups, rule->streamk != 0, M, N, K, split);
+    const int64_t chain =
+        pk::chain_of(rule->bm, rule->bn, rule->bk, rule->kgroups, rule->streamk != 0, M, N, K, rule_splits);
+    const int i = pk::cheapest(f, M, N, K, ws_bytes, chain, usable, &s, &us);
+    auto faster_than = [&](const Config *c, int split, float margin) {
+        const int t = cost_tile(f, c);
+        return t < 0 || us <= margin * pk::predict_us(f, f.tiles[t], M, N, K, split);
     };
-    int i = pk::cheapest(f, M, N, K, ws_bytes, chain(want), usable, &s, &us);
-    if (i < 0 && rs < want) {
-        i = pk::cheapest(f, M, N, K, ws_bytes, chain(rs), usable, &s, &us);
-        want = rs;
-    }
-    const int r = cost_tile(f, rule);
-    auto beats_rule = [&](int split) {
-        return r < 0 || us <= kCostMargin * pk::predict_us(f, f.tiles[r], M, N, K, split);
-    };
-    if (i < 0 || !(beats_rule(want) || beats_rule(rs))) {
-        *splits = rs;
+    const bool less = i >= 0 && (s < rule_splits || (rule->streamk && !cfgs[i]->streamk));
+    if (i < 0 || !faster_than(rule, rule_splits, kCostMargin) || (less && !faster_than(bare, 1, 1.f))) {
+        *splits = rule_splits;
         return rule;
     }
     *splits = s;
@@ -527,11 +526,15 @@ const Config *select_gemm_rule(int ta, int tb, int64_t M, int64_t N, int64_t K, 
 }
 
 // The configuration of a product that no table entry serves, and its split of
-// K as far as ws_bytes of workspace hold the partial sums: the tile and split
-// of the least predicted time, unless the rule's choice above (its split:
-// gemm_splits) is within 10 % of it; always the rule's B-resident form (one
-// pass over A and C; not in the model) and its register-staged tiles where no
-// direct-to-LDS form can address the operands.
+// K: the tile and split of the least predicted time, unless the rule's choice
+// above (its split: gemm_splits) is within 10 % of it; always the rule's
+// B-resident form (one pass over A and C; not in the model) and its
+// register-staged tiles where no direct-to-LDS form can address the operands.
+// Where ws_bytes of workspace hold that choice's partial sums it stands, so a
+// workspace of just the queried size serves as well as a larger one; with less,
+// the choice is made anew against what the rule can run there (judged by the
+// split the rule cannot have, some calls without a workspace took a shorter
+// chain of additions and up to 1.05 times the time, convolutions 1.13).
 const Config *predict_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
                            bool vec_ok, size_t ws_bytes, int *splits)
 {
@@ -542,10 +545,12 @@ const Config *predict_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int6
     *splits = 1;
     const Config *rule = select_gemm_rule(ta, tb, M, N, K, lda, ldb, ldc, vec_ok);
     if (!rule || rule->bres) return rule;
+    auto usable = [&](int t) { return k.c[l][t] && dma_fits(k.c[l][t], lda, ldb); };
     const int want = gemm_splits(rule, M, N, K);
-    const bool room = want <= 1 || ws_bytes >= (size_t)want * (size_t)M * (size_t)N * sizeof(float);
-    return choose(f, k.c[l], rule, M, N, K, ws_bytes, want, room ? want : 1,
-                  [&](int t) { return k.c[l][t] && dma_fits(k.c[l][t], lda, ldb); }, splits);
+    const Config *c = choose(f, k.c[l], rule, rule, M, N, K, SIZE_MAX, want, usable, splits);
+    if (splits_fit(*splits, M, N, ws_bytes)) return c;
+    return choose(f, k.c[l], rule, rule, M, N, K, ws_bytes, splits_fit(want, M, N, ws_bytes) ? want : 1, usable,
+                  splits);
 }
 
 const Config *select_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
@@ -576,6 +581,17 @@ bool conv_config_fits(const Config *c, bool va4, bool vb4)
 }
 
 int choose_splits(const Config *c, int64_t M, int64_t N, int64_t K);
+
+// Stream-K plan of an M x N x K product on configuration c: tiles, K-blocks
+// per tile, work-groups (the CUs' resident capacity, at most one per
+// iteration, a multiple of the XCD count) and the workspace layout: 2 partial
+// tiles per work-group, then one arrival counter per tile (256-byte aligned).
+struct SkPlan {
+    int tiles, nkb, groups;
+    size_t cnt_off, bytes;
+};
+
+bool streamk_plan(const Config *c, int64_t M, int64_t N, int64_t K, SkPlan *pl);
 
 // Convolutions that no table entry serves, Cin and Cout multiples of 4
 // (16-byte gathers): rules from the automated search over the paper's layers
@@ -618,24 +634,36 @@ const Config *select_conv_rule(int64_t M, int64_t Cout, int64_t K, bool va4, boo
 }
 
 // The configuration of a convolution that no table entry serves, and its
-// split of the reduction as far as ws_bytes hold the partial sums: the tile
-// and split of the least predicted time, unless the rule's choice above (its
-// split: choose_splits) is within 10 % of it.  Convolutions whose image (or
-// filter rows) the direct-to-LDS forms cannot address run the rule's
-// register-staged tiles.
+// split of the reduction: the tile and split of the least predicted time,
+// unless the rule's choice above (its split: choose_splits) is within 10 % of
+// it; with less workspace than that choice needs, made anew as for products
+// (predict_gemm).  Convolutions whose image (or filter rows) the direct-to-LDS
+// forms cannot address run the rule's register-staged tiles.
 const Config *predict_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool dma_ok, bool allow_sk,
                            size_t ws_bytes, int *splits)
 {
     static const CostConfigs k44(pk::kCostConv44, false), k41(pk::kCostConv41, false), k11(pk::kCostConv11, false);
     const pk::CostFamily &f = va4 && vb4 ? pk::kCostConv44 : va4 ? pk::kCostConv41 : pk::kCostConv11;
     const CostConfigs &k = va4 && vb4 ? k44 : va4 ? k41 : k11;
-    *splits = 1;
+    // the choice at room for `room` bytes, the rule's split cut to fit
+    auto at = [&](bool sk, size_t room) -> const Config * {
+        *splits = 1;
+        const Config *rule = select_conv_rule(M, Cout, K, va4, vb4, dma_ok, sk);
+        if (!rule) return nullptr;
+        const Config *bare = rule->streamk ? select_conv_rule(M, Cout, K, va4, vb4, dma_ok, false) : rule;
+        const int want = rule->streamk ? 1 : choose_splits(rule, M, Cout, K);
+        return choose(f, k.c[0], rule, bare, M, Cout, K, room, splits_fit(want, M, Cout, room) ? want : 1,
+                      [&](int t) { return dma_ok && k.c[0][t] && (sk || !f.tiles[t].streamk); }, splits);
+    };
+    const Config *c = at(allow_sk, SIZE_MAX);
+    SkPlan plan;
+    const bool room = !c || (c->streamk ? streamk_plan(c, M, Cout, K, &plan) && ws_bytes >= plan.bytes
+                                        : splits_fit(*splits, M, Cout, ws_bytes));
+    if (room) return c;
+    // a stream-K rule without room for its plan gives way first
     const Config *rule = select_conv_rule(M, Cout, K, va4, vb4, dma_ok, allow_sk);
-    if (!rule) return nullptr;
-    const int want = rule->streamk ? 1 : choose_splits(rule, M, Cout, K);
-    const bool room = want <= 1 || ws_bytes >= (size_t)want * (size_t)M * (size_t)Cout * sizeof(float);
-    return choose(f, k.c[0], rule, M, Cout, K, ws_bytes, want, room ? want : 1,
-                  [&](int t) { return dma_ok && k.c[0][t] && (allow_sk || !f.tiles[t].streamk); }, splits);
+    const bool sk = allow_sk && (!rule->streamk || (streamk_plan(rule, M, Cout, K, &plan) && ws_bytes >= plan.bytes));
+    return at(sk, ws_bytes);
 }
 
 const Config *select_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool dma_ok, bool allow_sk,
@@ -715,15 +743,6 @@ int xcd_count()
     const int x = env_int("PK_XCDS", 8);
     return x < 1 ? 1 : x;
 }
-
-// Stream-K plan of an M x N x K product on configuration c: tiles, K-blocks
-// per tile, work-groups (the CUs' resident capacity, at most one per
-// iteration, a multiple of the XCD count) and the workspace layout: 2 partial
-// tiles per work-group, then one arrival counter per tile (256-byte aligned).
-struct SkPlan {
-    int tiles, nkb, groups;
-    size_t cnt_off, bytes;
-};
 
 bool streamk_plan(const Config *c, int64_t M, int64_t N, int64_t K, SkPlan *pl)
 {

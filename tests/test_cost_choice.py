@@ -128,3 +128,27 @@ def test_choice_has_no_longer_chain_than_the_rules(choice):
         assert _chain(pick, *c[:3]) <= _chain(rule, *c[:3]), c
         streamk += rule.streamk and not pick.streamk
     assert streamk >= 50  # the stream-K rule's own regime is among them
+
+
+def test_choice_at_less_workspace(choice):
+    """A workspace of just what the choice asks for gives the same choice as a
+    larger one; with any less, the choice is neither predicted slower nor longer
+    in its chain than what the rule runs there."""
+    rng = random.Random(12)
+
+    def check(fn, args, M, N, K, factors):
+        _, full = choice(fn, *args, ALL_ROOM)
+        if not full.streamk:
+            need = full.splits * M * N * 4 if full.splits > 1 else 0
+            _, same = choice(fn, *args, need)
+            assert [getattr(same, n) for n, _ in _Pick._fields_] == [getattr(full, n) for n, _ in _Pick._fields_], args
+        for f in factors:
+            rule, pick = choice(fn, *args, int(f * M * N * 4))
+            assert _chain(pick, M, N, K) <= _chain(rule, M, N, K), (args, f)
+            if rule.us >= 0 and pick.us >= 0:
+                assert pick.us <= rule.us * (1 + 1e-6), (args, f)
+
+    for p in PRODUCTS + list(_products(rng, 8000)):
+        check("shim_gemm", p, *p[2:5], (0, rng.randint(2, 16)))
+    for c in _convs(rng, 8000):
+        check("shim_conv", c, *c[:3], (0, rng.randint(2, 16)))
