@@ -763,6 +763,144 @@ bool streamk_plan(const Config *c, int64_t M, int64_t N, int64_t K, SkPlan *pl)
     return true;
 }
 
+// What a call runs: a configuration and its split of K, or its stream-K plan.
+struct Choice {
+    const Config *c = nullptr;
+    int splits = 1;
+    SkPlan sk;
+};
+
+// Bytes of workspace a choice uses for an M x N result.
+size_t choice_bytes(const Choice &ch, int64_t M, int64_t N)
+{
+    if (ch.c->streamk) return ch.sk.bytes;
+    return ch.splits > 1 ? (size_t)ch.splits * (size_t)M * (size_t)N * sizeof(float) : 0;
+}
+
+// The split of a chosen configuration: the thread's forced one, else the one
+// that came with the choice (0: by_rule), if ws_bytes hold it.
+int settle_splits(Choice *ch, int splits, int by_rule, int64_t M, int64_t N, size_t ws_bytes)
+{
+    if (t_forced_splits > 0) {
+        ch->splits = t_forced_splits;
+        if (ch->splits > 1 && ch->c->bres) return PK_ERR_NOT_SUPPORTED;
+        return splits_fit(ch->splits, M, N, ws_bytes) ? PK_OK : PK_ERR_WORKSPACE;
+    }
+    ch->splits = splits > 0 ? splits : by_rule;
+    if (!splits_fit(ch->splits, M, N, ws_bytes)) ch->splits = 1;
+    return PK_OK;
+}
+
+// The choice for a product with ws_bytes of workspace (ws16: 16-byte aligned,
+// for stream-K): a forced configuration, a measured one, the selection.  One
+// function for the call and for its workspace query, which asks with SIZE_MAX.
+int gemm_choice(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool vec_ok,
+                size_t ws_bytes, bool ws16, Choice *ch)
+{
+    bool bad = false;
+    const Config *c = forced(&bad);
+    if (bad) return invalid(0);  // PK_FORCE_CONFIG names no configuration
+    auto fits = [&](const Config *k) {
+        return gemm_config_fits(k, ta, tb, vec_ok) && bres_fits(k, N, K, ldc) && dma_fits(k, lda, ldb);
+    };
+    auto streamk_ok = [&](const Config *k) {
+        return streamk_plan(k, M, N, K, &ch->sk) && ws_bytes >= ch->sk.bytes && ws16;
+    };
+    int splits = 0;  // 0: the rule's
+    if (c) {
+        if (!fits(c)) return PK_ERR_NOT_SUPPORTED;
+        if (c->streamk && !streamk_ok(c))
+            return streamk_plan(c, M, N, K, &ch->sk) ? PK_ERR_WORKSPACE : PK_ERR_NOT_SUPPORTED;
+    } else {
+        TunedShape t;
+        if (find_tuned(0, ta, tb, M, N, K, 0, 0, &t)) c = find_config(t.config);
+        if (c && (!fits(c) || (c->streamk && !streamk_ok(c)))) c = nullptr;
+        if (c)
+            splits = t.splits;
+        else
+            c = select_gemm(ta, tb, M, N, K, lda, ldb, ldc, vec_ok, ws_bytes, &splits);
+        if (!c) return PK_ERR_NOT_SUPPORTED;
+    }
+    ch->c = c;
+    ch->splits = 1;
+    return c->streamk ? PK_OK : settle_splits(ch, splits, gemm_splits(c, M, N, K), M, N, ws_bytes);
+}
+
+// A convolution's sizes: M = N*Ho*Wo outputs of K = KH*KW*Cin products each.
+struct ConvDims {
+    int64_t N, H, W, Cin, KH, KW, Cout, sh, sw, Ho, Wo, M, K;
+    bool gemm_path;  // 1x1, stride 1, no padding: the image is already the M x Cin matrix
+};
+
+// ... for a convolution (x16, f16: image and filter 16-byte aligned).
+int conv_choice(const ConvDims &d, bool x16, bool f16, size_t ws_bytes, bool ws16, Choice *ch)
+{
+    bool bad = false;
+    const Config *c = forced(&bad);
+    if (bad) return invalid(0);  // PK_FORCE_CONFIG names no configuration
+    const bool was_forced = c != nullptr;
+    const bool va4 = d.Cin % 4 == 0 && x16, vb4 = d.Cout % 4 == 0 && f16;
+    // the direct-to-LDS gather addresses the image in 32-bit byte offsets
+    const bool dma_ok = conv_dma_ok(d.N, d.H, d.W, d.Cin, d.Cout);
+    auto fits = [&](const Config *k) {
+        if (d.gemm_path)
+            return gemm_config_fits(k, 0, 0, va4 && vb4) && bres_fits(k, d.Cout, d.Cin, d.Cout) &&
+                   dma_fits(k, d.Cin, d.Cout);
+        if (k->kind == pk::KIND_DIRECT)  // (the persistent tiled form addresses an image in 32-bit byte offsets)
+            return d.N <= 65535 && pk::direct_conv_fits(k, d.W, d.Wo, d.Cout, d.KH, d.KW, d.Cin, d.sh, d.sw) &&
+                   (k->vec_a == 1 || va4) &&
+                   (k->tile_rows == 0 || !k->persistent || d.H * d.W * d.Cin < ((int64_t)1 << 29));
+        return conv_config_fits(k, va4, vb4) && (!k->dma || dma_ok);
+    };
+    int splits = 0;  // 0: the rule's
+    auto select = [&](bool allow_sk) {
+        return d.gemm_path ? select_gemm(0, 0, d.M, d.Cout, d.Cin, d.Cin, d.Cout, d.Cout, va4 && vb4, ws_bytes, &splits)
+                           : select_conv(d.M, d.Cout, d.K, va4, vb4, dma_ok, allow_sk, ws_bytes, &splits);
+    };
+    TunedShape t;
+    const bool tuned = d.KH == d.KW && d.sh == d.sw &&
+                       find_tuned(conv_kind(d.gemm_path), 0, 0, d.M, d.Cout, d.K, d.KH, d.sh, &t);
+    if (c) {
+        if (!fits(c)) return PK_ERR_NOT_SUPPORTED;
+        if (tuned && strcmp(c->name, t.config) == 0) splits = t.splits;
+    } else {
+        // a measured choice first (it may name a direct kernel), then the
+        // persistent direct form when its patch fits, else the
+        // one-tile-per-work-group form, then the selection
+        if (tuned) c = find_config(t.config);
+        if (c && !fits(c)) c = nullptr;
+        if (c) splits = t.splits;
+        if (!c && !d.gemm_path) {
+            for (const char *name : {"direct_8x32x64_k32_p", "direct_8x32x64_k32"}) {
+                const Config *k = find_config(name);
+                if (k && fits(k)) {
+                    c = k;
+                    break;
+                }
+            }
+        }
+        if (!c) c = select(ws16);
+        // a forced split needs a form that splits K across work-groups
+        if (c && t_forced_splits > 1 && c->bres)
+            c = find_config(va4 && vb4 ? "gemm_64x64x32_w2x2_nn_v44" : "gemm_64x64x16_w2x2_nn_v11");
+        if (!c) return PK_ERR_NOT_SUPPORTED;
+    }
+    // stream-K needs its partial tiles and counters in the workspace; without
+    // room for them the rules choose again (a forced choice reports it)
+    if (c->streamk) {
+        const bool planned = streamk_plan(c, d.M, d.Cout, d.K, &ch->sk);
+        if (!(planned && ws_bytes >= ch->sk.bytes && ws16)) {
+            if (was_forced) return planned ? PK_ERR_WORKSPACE : PK_ERR_NOT_SUPPORTED;
+            c = select(false);
+            if (!c) return PK_ERR_NOT_SUPPORTED;
+        }
+    }
+    ch->c = c;
+    ch->splits = 1;
+    if (c->streamk || c->kind == pk::KIND_DIRECT) return PK_OK;
+    return settle_splits(ch, splits, choose_splits(c, d.M, d.Cout, d.K), d.M, d.Cout, ws_bytes);
+}
+
 void fill_common(KernelArgs &a, const Config *c, int64_t M, int64_t N, int64_t K, int splits)
 {
     a.M = (int)M;
@@ -970,34 +1108,10 @@ int pk_sgemm_ws(char transA, char transB, int64_t M, int64_t N, int64_t K, float
     if (overlap(c0, c1, a0, a1) || overlap(c0, c1, b0, b1)) return invalid(12);
     if (!workspace) workspace_bytes = 0;
 
-    const bool vec_ok = gemm_vec_ok(ta, tb, M, N, K, A, lda, B, ldb);
-    bool bad = false;
-    const Config *c = forced(&bad);
-    if (bad) return invalid(0);  // PK_FORCE_CONFIG names no configuration
-    const bool was_forced = c != nullptr;
-    int splits = 0;  // 0: the rule's
-    SkPlan skp;
-    auto streamk_ok = [&](const Config *k) {
-        return streamk_plan(k, M, N, K, &skp) && workspace_bytes >= skp.bytes && aligned16(workspace);
-    };
-    if (c) {
-        if (!gemm_config_fits(c, ta, tb, vec_ok) || !bres_fits(c, N, K, ldc) || !dma_fits(c, lda, ldb))
-            return PK_ERR_NOT_SUPPORTED;
-        if (c->streamk && !streamk_ok(c)) return streamk_plan(c, M, N, K, &skp) ? PK_ERR_WORKSPACE : PK_ERR_NOT_SUPPORTED;
-    } else {
-        TunedShape tbuf;
-        const TunedShape *t = find_tuned(0, ta, tb, M, N, K, 0, 0, &tbuf) ? &tbuf : nullptr;
-        c = t ? find_config(t->config) : nullptr;
-        if (c && (!gemm_config_fits(c, ta, tb, vec_ok) || !bres_fits(c, N, K, ldc) || !dma_fits(c, lda, ldb) ||
-                  (c->streamk && !streamk_ok(c))))
-            c = nullptr;
-        if (c)
-            splits = t->splits;
-        else
-            c = select_gemm(ta, tb, M, N, K, lda, ldb, ldc, vec_ok, workspace_bytes, &splits);
-        if (!c) return PK_ERR_NOT_SUPPORTED;
-    }
-    (void)was_forced;
+    Choice ch;
+    const int st = gemm_choice(ta, tb, M, N, K, lda, ldb, ldc, gemm_vec_ok(ta, tb, M, N, K, A, lda, B, ldb),
+                               workspace_bytes, aligned16(workspace), &ch);
+    if (st != PK_OK) return st;
     KernelArgs a;
     memset(&a, 0, sizeof(a));
     a.A = A;
@@ -1014,30 +1128,21 @@ int pk_sgemm_ws(char transA, char transB, int64_t M, int64_t N, int64_t K, float
         const uintptr_t w1 = w0 + bytes;
         return overlap(w0, w1, a0, a1) || overlap(w0, w1, b0, b1) || overlap(w0, w1, c0, c1);
     };
-    if (c->streamk) {
-        if (ws_overlaps(skp.bytes)) return invalid(14);
-        fill_common(a, c, M, N, K, 1);
-        a.sk_nkb = skp.nkb;
-        a.sk_groups = skp.groups;
+    if (ch.c->streamk) {
+        if (ws_overlaps(ch.sk.bytes)) return invalid(14);
+        fill_common(a, ch.c, M, N, K, 1);
+        a.sk_nkb = ch.sk.nkb;
+        a.sk_groups = ch.sk.groups;
         a.sk_part = (float *)workspace;
-        a.sk_cnt = (int *)((char *)workspace + skp.cnt_off);
-        return launch(c, a, s);
+        a.sk_cnt = (int *)((char *)workspace + ch.sk.cnt_off);
+        return launch(ch.c, a, s);
     }
-    const size_t per_split = (size_t)M * (size_t)N * sizeof(float);
-    if (t_forced_splits > 0) {
-        splits = t_forced_splits;
-        if (splits > 1 && c->bres) return PK_ERR_NOT_SUPPORTED;
-        if (splits > 1 && workspace_bytes < (size_t)splits * per_split) return PK_ERR_WORKSPACE;
-    } else {
-        if (splits < 1) splits = gemm_splits(c, M, N, K);
-        if (splits > 1 && workspace_bytes < (size_t)splits * per_split) splits = 1;
-    }
-    fill_common(a, c, M, N, K, splits);
+    fill_common(a, ch.c, M, N, K, ch.splits);
     if (a.splits > 1) {
-        if (ws_overlaps((size_t)a.splits * per_split)) return invalid(14);
+        if (ws_overlaps((size_t)a.splits * (size_t)M * (size_t)N * sizeof(float))) return invalid(14);
         a.ws = (float *)workspace;
     }
-    return launch(c, a, s);
+    return launch(ch.c, a, s);
 }
 
 int pk_sgemm(char transA, char transB, int64_t M, int64_t N, int64_t K, float alpha, const float *A,
@@ -1052,33 +1157,14 @@ size_t pk_sgemm_workspace_bytes(char transA, char transB, int64_t M, int64_t N, 
     if (ta < 0 || tb < 0 || M < 1 || N < 1 || K < 1) return 0;
     if (M > kMaxDim || N > kMaxDim || K > kMaxDim) return 0;
     // the choice the next call on this thread makes for 16-byte aligned,
-    // tightly packed operands: a forced configuration, else the measured one,
-    // else the rules
-    const bool vec_ok = gemm_vec_ok(ta, tb, M, N, K, nullptr, ta ? M : K, nullptr, tb ? K : N);
-    bool bad = false;
-    const Config *c = forced(&bad);
-    if (bad) return 0;
-    int splits = 0;
-    if (!c) {
-        TunedShape tbuf;
-        if (find_tuned(0, ta, tb, M, N, K, 0, 0, &tbuf)) {
-            c = find_config(tbuf.config);
-            splits = tbuf.splits;
-        }
-        if (c && !gemm_config_fits(c, ta, tb, vec_ok)) c = nullptr;
-        if (!c) {
-            c = select_gemm(ta, tb, M, N, K, ta ? M : K, tb ? K : N, N, vec_ok, SIZE_MAX, &splits);
-        }
-    }
-    if (!c || !gemm_config_fits(c, ta, tb, vec_ok)) return 0;
-    if (c->streamk) {
-        SkPlan plan;
-        return streamk_plan(c, M, N, K, &plan) ? plan.bytes : 0;
-    }
-    if (t_forced_splits > 0) splits = t_forced_splits;
-    if (splits < 1) splits = gemm_splits(c, M, N, K);
-    if (c->bres || splits <= 1) return 0;
-    return (size_t)splits * (size_t)M * (size_t)N * sizeof(float);
+    // tightly packed operands
+    const int64_t lda = ta ? M : K, ldb = tb ? K : N;
+    Choice ch;
+    const int saved = t_last_param;
+    const int st = gemm_choice(ta, tb, M, N, K, lda, ldb, N, gemm_vec_ok(ta, tb, M, N, K, nullptr, lda, nullptr, ldb),
+                               SIZE_MAX, true, &ch);
+    t_last_param = saved;
+    return st == PK_OK ? choice_bytes(ch, M, N) : 0;
 }
 
 size_t pk_conv2d_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin, int64_t KH, int64_t KW,
@@ -1088,53 +1174,18 @@ size_t pk_conv2d_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin, i
     int64_t Ho = 0, Wo = 0;
     if (N < 1 || Cin < 1 || Cout < 1) return 0;
     const int saved = t_last_param;
-    const int st = out_dims(H, W, KH, KW, sh, sw, pt, pl, pb, pr, &Ho, &Wo, 2);
+    int st = out_dims(H, W, KH, KW, sh, sw, pt, pl, pb, pr, &Ho, &Wo, 2);
     t_last_param = saved;
     if (st != PK_OK) return 0;
     const bool gemm_path = KH == 1 && KW == 1 && sh == 1 && sw == 1 && pt == 0 && pl == 0 && pb == 0 && pr == 0;
     const int64_t M = checked_mul3(N, Ho, Wo), K = checked_mul3(KH, KW, Cin);
     if (M < 0 || K < 0 || M > kMaxDim || K > kMaxDim || Cout > kMaxDim) return 0;
     // the choice the next call on this thread makes for 16-byte aligned
-    // tensors (what the allocator gives): a forced configuration, else the
-    // measured one, else the rules
-    const bool v4 = Cin % 4 == 0 && Cout % 4 == 0;
-    bool bad = false;
-    const Config *c = forced(&bad);
-    if (bad) return 0;
-    const TunedShape *tuned = nullptr;
-    TunedShape tbuf;
-    int picked = 0;  // the selection's split; 0: a forced or measured configuration
-    if (!c) {
-        tuned = (KH == KW && sh == sw && find_tuned(conv_kind(gemm_path), 0, 0, M, Cout, K, KH, sh, &tbuf)) ? &tbuf
-                                                                                                         : nullptr;
-        // a measured direct configuration (any channel count) needs no workspace
-        const Config *td = tuned ? find_config(tuned->config) : nullptr;
-        if (!gemm_path && td && td->kind == pk::KIND_DIRECT && N <= 65535 &&
-            pk::direct_conv_fits(td, W, Wo, Cout, KH, KW, Cin, sh, sw))
-            return 0;
-        const bool direct_ok = !gemm_path && pk::direct_conv_fits(nullptr, W, Wo, Cout, KH, KW, Cin, sh, sw) && N <= 65535;
-        if (direct_ok && !(tuned && v4)) return 0;
-        c = (tuned && v4) ? td : nullptr;
-        // a table entry of the other path (never recorded, but checked) is ignored
-        if (c && (gemm_path ? !gemm_config_fits(c, 0, 0, v4) : !conv_config_fits(c, true, true))) {
-            c = nullptr;
-            tuned = nullptr;
-        }
-        if (!c)
-            c = gemm_path ? select_gemm(0, 0, M, Cout, Cin, Cin, Cout, Cout, v4, SIZE_MAX, &picked)
-                          : select_conv(M, Cout, K, Cin % 4 == 0, Cout % 4 == 0, conv_dma_ok(N, H, W, Cin, Cout), true,
-                                        SIZE_MAX, &picked);
-    }
-    if (!c || c->kind == pk::KIND_DIRECT) return 0;
-    if (c->streamk) {
-        SkPlan plan;
-        return streamk_plan(c, M, Cout, K, &plan) ? plan.bytes : 0;
-    }
-    if (tuned && v4 && tuned->splits > 0 && t_forced_splits == 0)
-        return tuned->splits > 1 ? (size_t)tuned->splits * (size_t)M * (size_t)Cout * sizeof(float) : 0;
-    const int splits = t_forced_splits > 0 ? t_forced_splits : picked ? picked : choose_splits(c, M, Cout, K);
-    if (splits <= 1) return 0;
-    return (size_t)splits * (size_t)M * (size_t)Cout * sizeof(float);
+    // tensors (what the allocator gives)
+    Choice ch;
+    st = conv_choice({N, H, W, Cin, KH, KW, Cout, sh, sw, Ho, Wo, M, K, gemm_path}, true, true, SIZE_MAX, true, &ch);
+    t_last_param = saved;
+    return st == PK_OK ? choice_bytes(ch, M, Cout) : 0;
 }
 
 int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, const float *f, int64_t KH,
@@ -1194,66 +1245,13 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, 
     a.alpha = 1.f;
     a.beta = 0.f;
 
-    bool bad = false;
-    const Config *c = forced(&bad);
-    if (bad) return invalid(0);  // PK_FORCE_CONFIG names no configuration
-    const bool was_forced = c != nullptr;
-    int picked = 0;  // the selection's split; 0: a forced or measured configuration
-    const size_t ws_room = workspace ? workspace_bytes : 0;
-
     const bool gemm_path = KH == 1 && KW == 1 && sh == 1 && sw == 1 && pt == 0 && pl == 0 && pb == 0 && pr == 0;
-    TunedShape tbuf;
-    const TunedShape *tuned =
-        (KH == KW && sh == sw && find_tuned(conv_kind(gemm_path), 0, 0, M, Cout, K, KH, sh, &tbuf)) ? &tbuf : nullptr;
-    // 1x1, stride 1, no padding: the image is already the M x Cin matrix
-    const bool vec_ok = gemm_path && gemm_vec_ok(0, 0, M, Cout, Cin, x, Cin, f, Cout);
-    const bool va4 = Cin % 4 == 0 && aligned16(x);
-    const bool vb4 = Cout % 4 == 0 && aligned16(f);
-    if (gemm_path) {
-        if (c) {
-            if (!gemm_config_fits(c, 0, 0, vec_ok) || !bres_fits(c, Cout, Cin, Cout) || !dma_fits(c, Cin, Cout))
-                return PK_ERR_NOT_SUPPORTED;
-        } else {
-            c = (tuned && vec_ok) ? find_config(tuned->config) : nullptr;
-            if (c && (!gemm_config_fits(c, 0, 0, vec_ok) || !bres_fits(c, Cout, Cin, Cout) || !dma_fits(c, Cin, Cout)))
-                c = nullptr;
-            if (!c) c = select_gemm(0, 0, M, Cout, Cin, Cin, Cout, Cout, vec_ok, ws_room, &picked);
-            // a forced split needs a form that splits K across work-groups
-            if (c && t_forced_splits > 1 && c->bres)
-                c = find_config(vec_ok ? "gemm_64x64x32_w2x2_nn_v44" : "gemm_64x64x16_w2x2_nn_v11");
-            if (!c) return PK_ERR_NOT_SUPPORTED;
-        }
-    } else {
-        // (the persistent tiled form addresses an image in 32-bit byte offsets)
-        auto direct_ok = [&](const Config *d) {
-            return N <= 65535 && pk::direct_conv_fits(d, W, Wo, Cout, KH, KW, Cin, sh, sw) &&
-                   (d->vec_a == 1 || va4) && (d->tile_rows == 0 || !d->persistent || H * W * Cin < ((int64_t)1 << 29));
-        };
-        // the direct-to-LDS gather addresses the image in 32-bit byte offsets
-        const bool dma_ok = conv_dma_ok(N, H, W, Cin, Cout);
-        if (c) {
-            if (!conv_config_fits(c, va4, vb4) || (c->dma && !dma_ok)) return PK_ERR_NOT_SUPPORTED;
-            if (c->kind == pk::KIND_DIRECT && !direct_ok(c)) return PK_ERR_NOT_SUPPORTED;
-        } else {
-            // a measured choice first (it may name the direct kernel), then the
-            // rules: the persistent direct form when its patch fits, else the
-            // one-tile-per-work-group form
-            c = tuned ? find_config(tuned->config) : nullptr;
-            if (c && (!conv_config_fits(c, va4, vb4) || (c->kind == pk::KIND_DIRECT && !direct_ok(c)) ||
-                      (c->dma && !dma_ok)))
-                c = nullptr;
-            if (!c) {
-                for (const char *name : {"direct_8x32x64_k32_p", "direct_8x32x64_k32"}) {
-                    const Config *d = find_config(name);
-                    if (d && direct_ok(d)) {
-                        c = d;
-                        break;
-                    }
-                }
-            }
-            if (!c) c = select_conv(M, Cout, K, va4, vb4, dma_ok, true, ws_room, &picked);
-        }
-        if (!c) return PK_ERR_NOT_SUPPORTED;
+    Choice ch;
+    const int st = conv_choice({N, H, W, Cin, KH, KW, Cout, sh, sw, Ho, Wo, M, K, gemm_path}, aligned16(x), aligned16(f),
+                               workspace ? workspace_bytes : 0, aligned16(workspace), &ch);
+    if (st != PK_OK) return st;
+    const Config *c = ch.c;
+    if (!gemm_path) {
         a.H = (int)H;
         a.W = (int)W;
         a.Cin = (int)Cin;
@@ -1267,37 +1265,13 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, 
         a.KH = (int)KH;
         a.batch = (int)N;
     }
-    // stream-K needs its partial tiles and counters in the workspace; without
-    // room for them the rules choose again (a forced choice reports it)
-    SkPlan skp;
-    bool streamk = false;
-    if (c->streamk) {
-        const bool planned = streamk_plan(c, M, Cout, K, &skp);
-        if (planned && workspace && workspace_bytes >= skp.bytes && aligned16(workspace)) {
-            streamk = true;
-        } else if (was_forced) {
-            return planned ? PK_ERR_WORKSPACE : PK_ERR_NOT_SUPPORTED;
-        } else {
-            c = gemm_path ? select_gemm(0, 0, M, Cout, Cin, Cin, Cout, Cout, vec_ok, ws_room, &picked)
-                          : select_conv(M, Cout, K, va4, vb4, conv_dma_ok(N, H, W, Cin, Cout), false, ws_room,
-                                        &picked);
-            if (!c) return PK_ERR_NOT_SUPPORTED;
-        }
-    }
-    if (streamk) {
-        a.A = x;
-        a.lda = Cin;
-        fill_common(a, c, M, Cout, K, 1);
-        const uintptr_t w0 = (uintptr_t)workspace, w1 = w0 + skp.bytes;
-        if (overlap(w0, w1, x0, x1) || overlap(w0, w1, f0, f1) || overlap(w0, w1, y0, y1)) return invalid(19);
-        a.sk_nkb = skp.nkb;
-        a.sk_groups = skp.groups;
-        a.sk_part = (float *)workspace;
-        a.sk_cnt = (int *)((char *)workspace + skp.cnt_off);
-        return launch(c, a, s);
-    }
+    a.A = x;
+    const uintptr_t w0 = (uintptr_t)workspace;
+    auto ws_overlaps = [&](size_t bytes) {
+        const uintptr_t w1 = w0 + bytes;
+        return overlap(w0, w1, x0, x1) || overlap(w0, w1, f0, f1) || overlap(w0, w1, y0, y1);
+    };
     if (c->kind == pk::KIND_DIRECT) {
-        a.A = x;
         a.M = (int)M;
         a.N = (int)Cout;
         a.K = (int)K;
@@ -1306,23 +1280,19 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, 
         t_last_config = c->name;
         return PK_OK;
     }
-    int splits = 1;
-    const size_t per_split = (size_t)M * (size_t)Cout * sizeof(float);
-    if (t_forced_splits > 0) {
-        splits = t_forced_splits;
-        if (splits > 1 && c->bres) return PK_ERR_NOT_SUPPORTED;
-        if (splits > 1 && (!workspace || workspace_bytes < (size_t)splits * per_split)) return PK_ERR_WORKSPACE;
-    } else {
-        const bool tuned_cfg = tuned && strcmp(c->name, tuned->config) == 0 && tuned->splits > 0;
-        splits = picked ? picked : tuned_cfg ? tuned->splits : choose_splits(c, M, Cout, K);
-        if (splits > 1 && (!workspace || workspace_bytes < (size_t)splits * per_split)) splits = 1;
-    }
-    a.A = x;
     a.lda = Cin;
-    fill_common(a, c, M, Cout, K, splits);
+    if (c->streamk) {
+        fill_common(a, c, M, Cout, K, 1);
+        if (ws_overlaps(ch.sk.bytes)) return invalid(19);
+        a.sk_nkb = ch.sk.nkb;
+        a.sk_groups = ch.sk.groups;
+        a.sk_part = (float *)workspace;
+        a.sk_cnt = (int *)((char *)workspace + ch.sk.cnt_off);
+        return launch(c, a, s);
+    }
+    fill_common(a, c, M, Cout, K, ch.splits);
     if (a.splits > 1) {
-        uintptr_t w0 = (uintptr_t)workspace, w1 = w0 + (size_t)a.splits * per_split;
-        if (overlap(w0, w1, x0, x1) || overlap(w0, w1, f0, f1) || overlap(w0, w1, y0, y1)) return invalid(19);
+        if (ws_overlaps((size_t)a.splits * (size_t)M * (size_t)Cout * sizeof(float))) return invalid(19);
         a.ws = (float *)workspace;
     }
     return launch(c, a, s);

@@ -51,4 +51,10 @@ void shim_conv(int64_t M, int64_t Cout, int64_t K, int va4, int vb4, size_t ws_b
     *pick = describe(f, c, M, Cout, K, held(s, M, Cout, ws_bytes));
 }
 
+// Records a measured configuration and split, as the automated search does.
+int shim_record(int kind, int64_t M, int64_t N, int64_t K, int window, int stride, const char *config, int splits)
+{
+    return record_tuned({kind, 0, 0, M, N, K, window, stride, find_config(config)->name, splits});
+}
+
 }  // extern "C"

@@ -152,3 +152,21 @@ def test_choice_at_less_workspace(choice):
         check("shim_gemm", p, *p[2:5], (0, rng.randint(2, 16)))
     for c in _convs(rng, 8000):
         check("shim_conv", c, *c[:3], (0, rng.randint(2, 16)))
+
+
+@pytest.mark.parametrize("n,h,cin,k,cout,config,splits", [
+    (1, 14, 129, 3, 130, "conv_64x64x32_w2x2_v11_dma2", 5), (1, 14, 132, 3, 130, "conv_64x64x32_w2x2_v41_dma2", 5),
+    (2, 21, 3, 7, 30, "conv_64x64x16_w2x2_v11", 3), (1, 14, 515, 1, 130, "gemm_64x64x32_w2x2_nn_v11_dma2", 5)])
+def test_measured_split_of_odd_channels_gets_its_workspace(pk, choice, n, h, cin, k, cout, config, splits):
+    """The workspace query asks for the split that the search recorded for a
+    convolution whose channels are no multiples of four."""
+    lib, M = choice.lib, n * h * h
+    lib.pk_conv2d_workspace_bytes.argtypes = [ctypes.c_int64] * 13
+    lib.pk_conv2d_workspace_bytes.restype = ctypes.c_size_t
+    size = [n, h, h, cin, k, k, cout, 1, 1] + [k // 2] * 4
+    assert lib.pk_conv2d_workspace_bytes(*size) != splits * M * cout * 4
+    try:
+        assert lib.shim_record(2 if k == 1 else 1, *map(ctypes.c_int64, (M, cout, k * k * cin)), k, 1, config.encode(), splits)
+        assert lib.pk_conv2d_workspace_bytes(*size) == splits * M * cout * 4
+    finally:
+        lib.pk_tune_reset()

@@ -106,3 +106,26 @@ def test_tuned_padded_1x1_does_not_reach_the_gemm_path():
         assert pk.conv2d_workspace_bytes(1, 56, 56, Cin, 1, 1, Cout, 1, 1, 0, 0, 0, 0) >= 0
     finally:
         pk.tune_reset()
+
+
+@pytest.mark.parametrize("window,cin,cout", [(3, 129, 130), (1, 515, 130)])
+def test_tuned_split_of_odd_channels_runs(window, cin, cout):
+    """The configuration and split that the search records for channel counts
+    that are no multiples of four run with the workspace the call asks for
+    itself: the same bits as with both forced."""
+    torch, pk = require_gpu()
+    rng = np.random.default_rng(304)
+    x = dev(wl.uniform(rng, 14 * 14 * cin).reshape(1, 14, 14, cin))
+    f = dev(wl.uniform(rng, window * window * cin * cout).reshape(window, window, cin, cout))
+    ws = torch.empty(16 * 14 * 14 * cout, dtype=torch.float32, device="cuda")
+    try:
+        r = pk.tune_conv2d(x, f, workspace=ws, iters=2)
+        y = pk.conv2d_fwd(x, f)
+        assert pk.last_config_name() == r["config"]
+        pk.force_config(r["config"])
+        pk.force_splits(r["splits"])
+        assert torch.equal(y, pk.conv2d_fwd(x, f, workspace=ws)), r
+    finally:
+        pk.force_config(None)
+        pk.force_splits(0)
+        pk.tune_reset()
