@@ -78,14 +78,18 @@ int pk_sgemm(char transA, char transB, int64_t M, int64_t N, int64_t K,
 /*
  * Bytes of device workspace that lets pk_sgemm_ws split the reduction K of
  * this product across work-groups, for the configuration the next
- * pk_sgemm_ws call on this thread would choose with 16-byte aligned, tightly
- * packed operands (a forced one included); 0 when that configuration needs
- * none.  A split keeps one M x N partial sum per slice of K; a stream-K
+ * pk_sgemm_ws call on this thread would choose (a forced one included); 0
+ * when that configuration needs none.  pk_sgemm_workspace_bytes answers for
+ * 16-byte aligned, tightly packed operands, pk_sgemm_workspace_bytes_for for
+ * the operands at hand (their alignment and leading dimensions; nothing is
+ * read).  A split keeps one M x N partial sum per slice of K; a stream-K
  * configuration two partial tiles per resident work-group and one arrival
  * counter per tile of C.  Products whose tiles fill the CUs take no split.
  * Host-only apart from an occupancy query of the kernel.
  */
 size_t pk_sgemm_workspace_bytes(char transA, char transB, int64_t M, int64_t N, int64_t K);
+size_t pk_sgemm_workspace_bytes_for(char transA, char transB, int64_t M, int64_t N, int64_t K,
+                                    const float *A, int64_t lda, const float *B, int64_t ldb, int64_t ldc);
 
 /*
  * pk_sgemm with a workspace (the same operation, arguments, quick returns
@@ -128,7 +132,9 @@ int pk_conv2d_same_pads(int64_t H, int64_t W, int64_t KH, int64_t KW,
  * Bytes of device workspace that lets pk_conv2d_fwd split the reduction
  * (KH * KW * Cin) of this problem across work-groups, for the configuration
  * the next pk_conv2d_fwd call on this thread would choose (a forced one
- * included); 0 when that configuration needs none.  A split-K configuration
+ * included); 0 when that configuration needs none.  The _for form answers for
+ * the tensors at hand (their alignment; nothing is read), the other for
+ * tensors of any alignment: the most that one of them asks for.  A split-K configuration
  * keeps one partial sum of y per slice of the reduction; a stream-K one keeps
  * two partial tiles per resident work-group and one arrival counter per tile
  * of y.  Host-only apart from an occupancy query of the kernel.
@@ -137,6 +143,10 @@ size_t pk_conv2d_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin,
                                  int64_t KH, int64_t KW, int64_t Cout,
                                  int64_t sh, int64_t sw, int64_t pt, int64_t pl,
                                  int64_t pb, int64_t pr);
+size_t pk_conv2d_workspace_bytes_for(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin,
+                                     const float *f, int64_t KH, int64_t KW, int64_t Cout,
+                                     int64_t sh, int64_t sw, int64_t pt, int64_t pl,
+                                     int64_t pb, int64_t pr);
 
 /*
  * 2-D convolution forward (Section 4.1, Algorithm 1 with a centred, zero-
@@ -171,7 +181,7 @@ int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin,
  * pk_conv2d_fwd for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * It runs exactly what pk_conv2d_fwd runs when given the workspace that
- * pk_conv2d_workspace_bytes() asks for (same configuration, split and
+ * pk_conv2d_workspace_bytes_for() asks for (same configuration, split and
  * results, bit for bit), with that workspace taken from a static device
  * buffer of PK_NOALLOC_SCRATCH_BYTES that the library holds on every device
  * it runs on until the process ends.  It calls no hipMalloc, hipFree or

@@ -63,11 +63,14 @@ SIGNATURES = {
     "pk_sgemm": (ctypes.c_int, [ctypes.c_char, ctypes.c_char, _i64, _i64, _i64, ctypes.c_float, _p, _i64,
                                 _p, _i64, ctypes.c_float, _p, _i64, _p]),
     "pk_sgemm_workspace_bytes": (ctypes.c_size_t, [ctypes.c_char, ctypes.c_char, _i64, _i64, _i64]),
+    "pk_sgemm_workspace_bytes_for": (ctypes.c_size_t, [ctypes.c_char, ctypes.c_char, _i64, _i64, _i64, _p, _i64,
+                                                       _p, _i64, _i64]),
     "pk_sgemm_ws": (ctypes.c_int, [ctypes.c_char, ctypes.c_char, _i64, _i64, _i64, ctypes.c_float, _p, _i64,
                                    _p, _i64, ctypes.c_float, _p, _i64, _p, ctypes.c_size_t, _p]),
     "pk_conv2d_out_dims": (ctypes.c_int, [_i64] * 10 + [_p, _p]),
     "pk_conv2d_same_pads": (ctypes.c_int, [_i64] * 6 + [_p]),
     "pk_conv2d_workspace_bytes": (ctypes.c_size_t, [_i64] * 13),
+    "pk_conv2d_workspace_bytes_for": (ctypes.c_size_t, [_p] + [_i64] * 4 + [_p] + [_i64] * 9),
     "pk_conv2d_fwd": (ctypes.c_int, [_p, _i64, _i64, _i64, _i64, _p, _i64, _i64, _i64,
                                      _i64, _i64, _i64, _i64, _i64, _i64, _p, _i64, _i64,
                                      _p, ctypes.c_size_t, _p]),
@@ -124,7 +127,7 @@ def load():
 # The native marshalling (csrc/pk_torch.cpp) of the plain tensor calls, bound to
 # the loaded library's entry points at first use.
 EXT_PATH = os.path.join(HERE, "_pk_torch.so")
-_NATIVE_ENTRIES = ("pk_sgemm_ws", "pk_sgemm_workspace_bytes", "pk_conv2d_fwd", "pk_conv2d_workspace_bytes",
+_NATIVE_ENTRIES = ("pk_sgemm_ws", "pk_sgemm_workspace_bytes_for", "pk_conv2d_fwd", "pk_conv2d_workspace_bytes_for",
                    "pk_conv2d_out_dims", "pk_conv2d_same_pads", "pk_conv2d_winograd_tile_fwd",
                    "pk_conv2d_winograd_tile_workspace_bytes")
 _native = None
@@ -355,7 +358,8 @@ def gemm(a, b, c=None, alpha=1.0, beta=0.0, trans_a=False, trans_b=False, worksp
         raise ValueError("c must be %d x %d" % (M, N))
     ldc = _ld_2d(c, "c")
     if workspace is None:
-        need = sgemm_workspace_bytes(bool(trans_a), bool(trans_b), M, N, K)
+        need = load().pk_sgemm_workspace_bytes_for(_trans(bool(trans_a)), _trans(bool(trans_b)), M, N, K,
+                                                   a.data_ptr(), lda, b.data_ptr(), ldb, ldc)
         if need:
             workspace = torch.empty((need + 3) // 4, dtype=torch.float32, device=a.device)
     ws_ptr, ws_bytes = None, 0
@@ -414,7 +418,8 @@ def conv2d_fwd(x, w, stride=(1, 1), padding="SAME", out=None, workspace=None):
         raise ValueError("out must be a contiguous %s tensor" % ((N, Ho, Wo, Cout),))
     ws_ptr, ws_bytes = None, 0
     if workspace is None:
-        need = conv2d_workspace_bytes(N, H, W, Cin, KH, KW, Cout, sh, sw, pt, pl, pb, pr)
+        need = load().pk_conv2d_workspace_bytes_for(x.data_ptr(), N, H, W, Cin, w.data_ptr(), KH, KW, Cout, sh, sw,
+                                                    pt, pl, pb, pr)
         if need:
             workspace = torch.empty((need + 3) // 4, dtype=torch.float32, device=x.device)
     if workspace is not None:

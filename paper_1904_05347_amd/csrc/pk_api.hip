@@ -638,9 +638,14 @@ const Config *select_conv_rule(int64_t M, int64_t Cout, int64_t K, bool va4, boo
 // unless the rule's choice above (its split: choose_splits) is within 10 % of
 // it; with less workspace than that choice needs, made anew as for products
 // (predict_gemm).  Convolutions whose image (or filter rows) the direct-to-LDS
-// forms cannot address run the rule's register-staged tiles.
-const Config *predict_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool dma_ok, bool allow_sk,
-                           size_t ws_bytes, int *splits)
+// forms cannot address run the rule's register-staged tiles.  whole4: the
+// channels are multiples of four; where only an address breaks the 16-byte
+// accesses, the rule splits as far as the aligned rule's workspace holds it
+// (beyond that its split cost reductions of 500 to 800 up to 1.27 times the
+// unsplit time; for odd channels, whose results always had the split's shorter
+// chains, it stands).
+const Config *predict_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool whole4, bool dma_ok,
+                           bool allow_sk, size_t ws_bytes, int *splits)
 {
     static const CostConfigs k44(pk::kCostConv44, false), k41(pk::kCostConv41, false), k11(pk::kCostConv11, false);
     const pk::CostFamily &f = va4 && vb4 ? pk::kCostConv44 : va4 ? pk::kCostConv41 : pk::kCostConv11;
@@ -651,7 +656,14 @@ const Config *predict_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb
         const Config *rule = select_conv_rule(M, Cout, K, va4, vb4, dma_ok, sk);
         if (!rule) return nullptr;
         const Config *bare = rule->streamk ? select_conv_rule(M, Cout, K, va4, vb4, dma_ok, false) : rule;
-        const int want = rule->streamk ? 1 : choose_splits(rule, M, Cout, K);
+        int want = rule->streamk ? 1 : choose_splits(rule, M, Cout, K);
+        if (whole4 && !(va4 && vb4)) {
+            const Config *r4 = select_conv_rule(M, Cout, K, true, true, dma_ok, sk);
+            SkPlan p4;
+            if (!(r4->streamk ? streamk_plan(r4, M, Cout, K, &p4) && splits_fit(want, M, Cout, p4.bytes)
+                              : want <= choose_splits(r4, M, Cout, K)))
+                want = 1;
+        }
         return choose(f, k.c[0], rule, bare, M, Cout, K, room, splits_fit(want, M, Cout, room) ? want : 1,
                       [&](int t) { return dma_ok && k.c[0][t] && (sk || !f.tiles[t].streamk); }, splits);
     };
@@ -666,13 +678,13 @@ const Config *predict_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb
     return at(sk, ws_bytes);
 }
 
-const Config *select_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool dma_ok, bool allow_sk,
-                          size_t ws_bytes, int *splits)
+const Config *select_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb4, bool whole4, bool dma_ok,
+                          bool allow_sk, size_t ws_bytes, int *splits)
 {
-    const int64_t key[8] = {M, Cout, K, 0, 0, 0, (int64_t)ws_bytes, 16 + 8 * va4 + 4 * vb4 + 2 * dma_ok + allow_sk};
+    const int64_t key[8] = {M, Cout, K, whole4, 0, 0, (int64_t)ws_bytes, 16 + 8 * va4 + 4 * vb4 + 2 * dma_ok + allow_sk};
     bool hit;
     Selection &m = memo_slot(key, &hit);
-    if (!hit) m.c = predict_conv(M, Cout, K, va4, vb4, dma_ok, allow_sk, ws_bytes, &m.splits);
+    if (!hit) m.c = predict_conv(M, Cout, K, va4, vb4, whole4, dma_ok, allow_sk, ws_bytes, &m.splits);
     *splits = m.splits;
     return m.c;
 }
@@ -855,7 +867,8 @@ int conv_choice(const ConvDims &d, bool x16, bool f16, size_t ws_bytes, bool ws1
     int splits = 0;  // 0: the rule's
     auto select = [&](bool allow_sk) {
         return d.gemm_path ? select_gemm(0, 0, d.M, d.Cout, d.Cin, d.Cin, d.Cout, d.Cout, va4 && vb4, ws_bytes, &splits)
-                           : select_conv(d.M, d.Cout, d.K, va4, vb4, dma_ok, allow_sk, ws_bytes, &splits);
+                           : select_conv(d.M, d.Cout, d.K, va4, vb4, d.Cin % 4 == 0 && d.Cout % 4 == 0, dma_ok, allow_sk,
+                                         ws_bytes, &splits);
     };
     TunedShape t;
     const bool tuned = d.KH == d.KW && d.sh == d.sw &&
@@ -1151,25 +1164,30 @@ int pk_sgemm(char transA, char transB, int64_t M, int64_t N, int64_t K, float al
     return pk_sgemm_ws(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, nullptr, 0, stream);
 }
 
-size_t pk_sgemm_workspace_bytes(char transA, char transB, int64_t M, int64_t N, int64_t K)
+size_t pk_sgemm_workspace_bytes_for(char transA, char transB, int64_t M, int64_t N, int64_t K, const float *A,
+                                    int64_t lda, const float *B, int64_t ldb, int64_t ldc)
 {
     const int ta = trans_flag(transA), tb = trans_flag(transB);
     if (ta < 0 || tb < 0 || M < 1 || N < 1 || K < 1) return 0;
     if (M > kMaxDim || N > kMaxDim || K > kMaxDim) return 0;
-    // the choice the next call on this thread makes for 16-byte aligned,
-    // tightly packed operands
-    const int64_t lda = ta ? M : K, ldb = tb ? K : N;
     Choice ch;
     const int saved = t_last_param;
-    const int st = gemm_choice(ta, tb, M, N, K, lda, ldb, N, gemm_vec_ok(ta, tb, M, N, K, nullptr, lda, nullptr, ldb),
-                               SIZE_MAX, true, &ch);
+    const int st = gemm_choice(ta, tb, M, N, K, lda, ldb, ldc, gemm_vec_ok(ta, tb, M, N, K, A, lda, B, ldb), SIZE_MAX,
+                               true, &ch);
     t_last_param = saved;
     return st == PK_OK ? choice_bytes(ch, M, N) : 0;
 }
 
-size_t pk_conv2d_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin, int64_t KH, int64_t KW,
-                                 int64_t Cout, int64_t sh, int64_t sw, int64_t pt, int64_t pl, int64_t pb,
-                                 int64_t pr)
+size_t pk_sgemm_workspace_bytes(char transA, char transB, int64_t M, int64_t N, int64_t K)
+{
+    // 16-byte aligned, tightly packed operands
+    const int64_t lda = trans_flag(transA) == 1 ? M : K, ldb = trans_flag(transB) == 1 ? K : N;
+    return pk_sgemm_workspace_bytes_for(transA, transB, M, N, K, nullptr, lda, nullptr, ldb, N);
+}
+
+size_t pk_conv2d_workspace_bytes_for(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, const float *f,
+                                     int64_t KH, int64_t KW, int64_t Cout, int64_t sh, int64_t sw, int64_t pt,
+                                     int64_t pl, int64_t pb, int64_t pr)
 {
     int64_t Ho = 0, Wo = 0;
     if (N < 1 || Cin < 1 || Cout < 1) return 0;
@@ -1180,12 +1198,28 @@ size_t pk_conv2d_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin, i
     const bool gemm_path = KH == 1 && KW == 1 && sh == 1 && sw == 1 && pt == 0 && pl == 0 && pb == 0 && pr == 0;
     const int64_t M = checked_mul3(N, Ho, Wo), K = checked_mul3(KH, KW, Cin);
     if (M < 0 || K < 0 || M > kMaxDim || K > kMaxDim || Cout > kMaxDim) return 0;
-    // the choice the next call on this thread makes for 16-byte aligned
-    // tensors (what the allocator gives)
     Choice ch;
-    st = conv_choice({N, H, W, Cin, KH, KW, Cout, sh, sw, Ho, Wo, M, K, gemm_path}, true, true, SIZE_MAX, true, &ch);
+    st = conv_choice({N, H, W, Cin, KH, KW, Cout, sh, sw, Ho, Wo, M, K, gemm_path}, aligned16(x), aligned16(f),
+                     SIZE_MAX, true, &ch);
     t_last_param = saved;
     return st == PK_OK ? choice_bytes(ch, M, Cout) : 0;
+}
+
+size_t pk_conv2d_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t Cin, int64_t KH, int64_t KW,
+                                 int64_t Cout, int64_t sh, int64_t sw, int64_t pt, int64_t pl, int64_t pb,
+                                 int64_t pr)
+{
+    // both tensors 16-byte aligned, the filter not, the image not (then the
+    // filter's alignment doesn't matter); addresses that are never read
+    const float *const odd = (const float *)sizeof(float);
+    const float *const at[3][2] = {{nullptr, nullptr}, {nullptr, odd}, {odd, odd}};
+    size_t most = 0;
+    for (const auto &p : at) {
+        const size_t b =
+            pk_conv2d_workspace_bytes_for(p[0], N, H, W, Cin, p[1], KH, KW, Cout, sh, sw, pt, pl, pb, pr);
+        if (b > most) most = b;
+    }
+    return most;
 }
 
 int pk_conv2d_fwd(const float *x, int64_t N, int64_t H, int64_t W, int64_t Cin, const float *f, int64_t KH,
@@ -1350,7 +1384,7 @@ int pk_conv2d_fwd_noalloc(const float *x, int64_t N, int64_t H, int64_t W, int64
 {
     // the workspace pk_conv2d_fwd would be given (0 also for arguments that
     // pk_conv2d_fwd then rejects with their positions)
-    const size_t need = pk_conv2d_workspace_bytes(N, H, W, Cin, KH, KW, Cout, sh, sw, pt, pl, pb, pr);
+    const size_t need = pk_conv2d_workspace_bytes_for(x, N, H, W, Cin, f, KH, KW, Cout, sh, sw, pt, pl, pb, pr);
     if (need > PK_NOALLOC_SCRATCH_BYTES) {
         begin();
         return PK_ERR_SCRATCH_LIMIT;

@@ -34,9 +34,9 @@ namespace {
 
 // the C-ABI of the library binding.py loaded (set once by bind())
 decltype(&pk_sgemm_ws) f_sgemm_ws;
-decltype(&pk_sgemm_workspace_bytes) f_sgemm_workspace_bytes;
+decltype(&pk_sgemm_workspace_bytes_for) f_sgemm_workspace_bytes;
 decltype(&pk_conv2d_fwd) f_conv2d_fwd;
-decltype(&pk_conv2d_workspace_bytes) f_conv2d_workspace_bytes;
+decltype(&pk_conv2d_workspace_bytes_for) f_conv2d_workspace_bytes;
 decltype(&pk_conv2d_out_dims) f_out_dims;
 decltype(&pk_conv2d_same_pads) f_same_pads;
 decltype(&pk_conv2d_winograd_tile_fwd) f_winograd;
@@ -141,12 +141,12 @@ PyObject *py_gemm(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     const int64_t ldc = ld_2d(c);
     if (ldc < 0) Py_RETURN_NONE;
     const char fa = ta ? 'T' : 'N', fb = tb ? 'T' : 'N';
+    const float *pa = (const float *)a->data_ptr(), *pb = (const float *)b->data_ptr();
     at::Tensor own;
     void *ws;
     size_t ws_bytes;
-    const size_t need = args[7] == Py_None ? f_sgemm_workspace_bytes(fa, fb, M, N, K) : 0;
+    const size_t need = args[7] == Py_None ? f_sgemm_workspace_bytes(fa, fb, M, N, K, pa, lda, pb, ldb, ldc) : 0;
     if (!workspace_for(args[7], need, *a, &own, &ws, &ws_bytes)) Py_RETURN_NONE;
-    const float *pa = (const float *)a->data_ptr(), *pb = (const float *)b->data_ptr();
     float *pc = (float *)c.data_ptr();
     void *stream = stream_of(c);
     int st;
@@ -238,14 +238,14 @@ PyObject *py_conv2d_fwd(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     if (nargs != 6 || args[2] == Py_None || modes_active() || !geometry(args[0], args[1], args[2], args[3], &g) ||
         !output_for(args[4], g, &y))
         Py_RETURN_NONE;
+    const float *px = (const float *)g.x->data_ptr(), *pw = (const float *)g.w->data_ptr();
     const size_t need = args[5] == Py_None
-                            ? f_conv2d_workspace_bytes(g.N, g.H, g.W, g.Cin, g.KH, g.KW, g.Cout, g.sh, g.sw, g.p[0],
-                                                       g.p[1], g.p[2], g.p[3])
+                            ? f_conv2d_workspace_bytes(px, g.N, g.H, g.W, g.Cin, pw, g.KH, g.KW, g.Cout, g.sh, g.sw,
+                                                       g.p[0], g.p[1], g.p[2], g.p[3])
                             : 0;
     void *ws;
     size_t ws_bytes;
     if (!workspace_for(args[5], need, *g.x, &own, &ws, &ws_bytes)) Py_RETURN_NONE;
-    const float *px = (const float *)g.x->data_ptr(), *pw = (const float *)g.w->data_ptr();
     float *py = (float *)y.data_ptr();
     void *stream = stream_of(y);
     int st;

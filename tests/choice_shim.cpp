@@ -35,9 +35,10 @@ void shim_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int vec, size_t 
     *pick = describe(f, c, M, N, K, held(s, M, N, ws_bytes));
 }
 
-// ... of a convolution (M outputs, K taps times channels); a stream-K form
-// without room for its plan gives way as it does in the call.
-void shim_conv(int64_t M, int64_t Cout, int64_t K, int va4, int vb4, size_t ws_bytes, shim_pick *rule, shim_pick *pick)
+// ... of a convolution (M outputs, K taps times channels; whole4: channels are
+// multiples of four, as for va4 and vb4); a stream-K form without room for its
+// plan gives way as it does in the call.
+void shim_conv(int64_t M, int64_t Cout, int64_t K, int va4, int vb4, int whole4, size_t ws_bytes, shim_pick *rule, shim_pick *pick)
 {
     const pk::CostFamily &f = va4 && vb4 ? pk::kCostConv44 : va4 ? pk::kCostConv41 : pk::kCostConv11;
     SkPlan plan;
@@ -46,8 +47,8 @@ void shim_conv(int64_t M, int64_t Cout, int64_t K, int va4, int vb4, size_t ws_b
     if (!room(r)) r = select_conv_rule(M, Cout, K, va4, vb4, true, false);
     *rule = describe(f, r, M, Cout, K, r->streamk ? 1 : held(choose_splits(r, M, Cout, K), M, Cout, ws_bytes));
     int s = 0;
-    const Config *c = select_conv(M, Cout, K, va4, vb4, true, true, ws_bytes, &s);
-    if (!room(c)) c = select_conv(M, Cout, K, va4, vb4, true, false, ws_bytes, &s);
+    const Config *c = select_conv(M, Cout, K, va4, vb4, whole4, true, true, ws_bytes, &s);
+    if (!room(c)) c = select_conv(M, Cout, K, va4, vb4, whole4, true, false, ws_bytes, &s);
     *pick = describe(f, c, M, Cout, K, held(s, M, Cout, ws_bytes));
 }
 

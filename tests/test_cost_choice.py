@@ -62,7 +62,7 @@ def choice(pk, tmp_path_factory):
     lib = ctypes.CDLL(out)
     i64, sz, p = ctypes.c_int64, ctypes.c_size_t, ctypes.POINTER(_Pick)
     lib.shim_gemm.argtypes = [ctypes.c_int, ctypes.c_int, i64, i64, i64, ctypes.c_int, sz, p, p]
-    lib.shim_conv.argtypes = [i64, i64, i64, ctypes.c_int, ctypes.c_int, sz, p, p]
+    lib.shim_conv.argtypes = [i64, i64, i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, sz, p, p]
 
     def call(fn, *args):
         rule, pick = _Pick(), _Pick()
@@ -105,15 +105,15 @@ STREAMK_CONVS = [(8, 35, 128, 3, 192, 1), (18, 24, 156, 3, 160, 1), (3, 118, 48,
 
 
 def _convs(rng, count):
-    """(M, Cout, K, 16-byte image, 16-byte filter)"""
+    """(M, Cout, K, 16-byte image, 16-byte filter, channels multiples of four)"""
     for n, h, cin, k, cout, s in STREAMK_CONVS:
-        yield n * (-(-h // s)) ** 2, cout, k * k * cin, 1, 1
+        yield n * (-(-h // s)) ** 2, cout, k * k * cin, 1, 1, 1
     for i in range(count):
         h, s, k = _log(rng, 7, 224), rng.choice([1, 1, 2]), rng.choice([1, 3, 3, 5, 7])
         M, K = _log(rng, 1, 32) * (-(-h // s)) ** 2, k * k * (_log(rng, 8, 1024) // 4 * 4)
         cout = max(4, _log(rng, 8, 1024) // 4 * 4)
         if M * cout * K < 4e10 and M * cout < 1e8:
-            yield M, cout, K, i % 4 < 3, i % 4 < 2
+            yield M, cout, K, i % 4 < 3, i % 4 < 2, i % 4 < 2
 
 
 def test_choice_has_no_longer_chain_than_the_rules(choice):
@@ -161,12 +161,48 @@ def test_measured_split_of_odd_channels_gets_its_workspace(pk, choice, n, h, cin
     """The workspace query asks for the split that the search recorded for a
     convolution whose channels are no multiples of four."""
     lib, M = choice.lib, n * h * h
-    lib.pk_conv2d_workspace_bytes.argtypes = [ctypes.c_int64] * 13
-    lib.pk_conv2d_workspace_bytes.restype = ctypes.c_size_t
-    size = [n, h, h, cin, k, k, cout, 1, 1] + [k // 2] * 4
-    assert lib.pk_conv2d_workspace_bytes(*size) != splits * M * cout * 4
+    lib.pk_conv2d_workspace_bytes_for.argtypes = pk.binding.SIGNATURES["pk_conv2d_workspace_bytes_for"][1]
+    lib.pk_conv2d_workspace_bytes_for.restype = ctypes.c_size_t
+    args = [None, n, h, h, cin, None, k, k, cout, 1, 1] + [k // 2] * 4
+    assert lib.pk_conv2d_workspace_bytes_for(*args) != splits * M * cout * 4
     try:
         assert lib.shim_record(2 if k == 1 else 1, *map(ctypes.c_int64, (M, cout, k * k * cin)), k, 1, config.encode(), splits)
-        assert lib.pk_conv2d_workspace_bytes(*size) == splits * M * cout * 4
+        assert lib.pk_conv2d_workspace_bytes_for(*args) == splits * M * cout * 4
     finally:
         lib.pk_tune_reset()
+
+
+def test_workspace_query_for_the_operands_at_hand(pk, choice):
+    """Operands aligned to 4 bytes only, or inside wider rows, get the workspace
+    of the choice made for them, not of the aligned operands' one; a
+    convolution's plain query holds every alignment's."""
+    lib, rng = pk.load(), random.Random(13)
+    differ = 0
+    for i in range(3000):
+        ta, tb, M, N, K, _ = next(_products(rng, 1))
+        M, N, K = max(4, M // 4 * 4), max(4, N // 4 * 4), max(4, K // 4 * 4)
+        _, pick = choice("shim_gemm", ta, tb, M, N, K, 0, ALL_ROOM)
+        need = pick.splits * M * N * 4 if pick.splits > 1 else 0
+        lda, ldb = (M if ta else K), (K if tb else N)
+        sizes = [b"NT"[ta:ta + 1], b"NT"[tb:tb + 1], M, N, K]
+        assert lib.pk_sgemm_workspace_bytes_for(*sizes, None, lda + 3, None, ldb, N) == need, sizes
+        assert lib.pk_sgemm_workspace_bytes_for(*sizes, 4, lda, None, ldb, N) == need, sizes
+        aligned = pk.binding.sgemm_workspace_bytes(bool(ta), bool(tb), M, N, K)
+        assert lib.pk_sgemm_workspace_bytes_for(*sizes, None, lda, None, ldb, N) == aligned
+        differ += aligned < need
+    assert differ > 50
+    differ = 0
+    for i in range(3000):
+        n, h, cin, cout, k = rng.randint(1, 32), _log(rng, 7, 100), 4 * _log(rng, 5, 200), 4 * _log(rng, 2, 200), rng.choice([3, 5])
+        if k * k * cin < 500:  # (a direct form may take those)
+            continue
+        size, pads = [h, h, cin], [k // 2] * 4
+        plain = pk.conv2d_workspace_bytes(n, h, h, cin, k, k, cout, 1, 1, *pads)
+        for x, f, v in ((4, None, 0), (4, 4, 0), (None, 4, 1)):
+            need = lib.pk_conv2d_workspace_bytes_for(x, n, *size, f, k, k, cout, 1, 1, *pads)
+            _, pick = choice("shim_conv", n * h * h, cout, k * k * cin, v, 0, 1, ALL_ROOM)
+            assert need == (pick.splits * n * h * h * cout * 4 if pick.splits > 1 else 0), (n, h, cin, cout, k)
+            aligned = lib.pk_conv2d_workspace_bytes_for(None, n, *size, None, k, k, cout, 1, 1, *pads)
+            assert plain >= max(need, aligned)
+            differ += aligned < need
+    assert differ > 50

@@ -38,3 +38,21 @@ def test_conv_choice_at_queried_workspace(n, h, w, cin, k, cout):
     x = torch.randn((n, h, w, cin), device="cuda")
     f = torch.randn((k, k, cin, cout), device="cuda")
     _same(torch, pk, lambda ws: pk.conv2d_fwd(x, f, workspace=ws))
+
+
+@pytest.mark.parametrize("M,N,K", [(12, 6920, 796), (284, 1996, 2776)])
+def test_sliced_gemm_choice_at_its_own_workspace(M, N, K):
+    """Operands inside wider rows get the workspace of their own choice."""
+    torch, pk = require_gpu()
+    a = torch.randn((K, M + 3), device="cuda")[:, :M]
+    b = torch.randn((N, K + 3), device="cuda")[:, :K]
+    _same(torch, pk, lambda ws: pk.gemm(a, b, trans_a=True, trans_b=True, workspace=ws))
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [(1, 56, 57, 460, 288), (2, 30, 31, 324, 52)])
+def test_conv_choice_at_4_byte_addresses(n, h, w, cin, cout):
+    """... and an image and a filter at addresses aligned to 4 bytes only."""
+    torch, pk = require_gpu()
+    x = torch.randn(1 + n * h * w * cin, device="cuda")[1:].view(n, h, w, cin)
+    f = torch.randn(1 + 9 * cin * cout, device="cuda")[1:].view(3, 3, cin, cout)
+    _same(torch, pk, lambda ws: pk.conv2d_fwd(x, f, workspace=ws))
