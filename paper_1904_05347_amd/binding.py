@@ -319,11 +319,14 @@ def _check_f32_cuda(t, what):
 
 
 def _ld_2d(t, what):
-    """Leading dimension of a row-major 2-D view (unit column stride)."""
+    """Leading dimension of a row-major 2-D view (unit column stride, rows that
+    do not overlap: an expanded row has no leading dimension)."""
     if t.dim() != 2:
         raise ValueError("%s must be 2-D" % what)
     if t.size(1) > 1 and t.stride(1) != 1:
         raise ValueError("%s must have unit column stride" % what)
+    if t.size(0) > 1 and t.stride(0) < t.size(1):
+        raise ValueError("the rows of %s must not overlap" % what)
     return max(t.stride(0), t.size(1), 1)
 
 

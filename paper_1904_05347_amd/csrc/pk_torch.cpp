@@ -63,10 +63,11 @@ bool modes_active()
     return at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set();
 }
 
-// Leading dimension of a row-major 2-D view, or -1.
+// Leading dimension of a row-major 2-D view whose rows do not overlap, or -1.
 int64_t ld_2d(const at::Tensor &t)
 {
     if (t.dim() != 2 || (t.size(1) > 1 && t.stride(1) != 1)) return -1;
+    if (t.size(0) > 1 && t.stride(0) < t.size(1)) return -1;
     return std::max<int64_t>(std::max(t.stride(0), t.size(1)), 1);
 }
 

@@ -430,3 +430,17 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
         pkg.load()
     with pytest.raises(pkg.PkLibraryMissing):
         pkg.conv2d_out_dims(8, 8, 3, 3, 1, 1, 1, 1, 1, 1)
+
+
+def test_leading_dimension_of_overlapping_rows_is_refused():
+    """A view whose rows overlap (an expanded row, a stride below the width) has
+    no leading dimension; read with one it would leave its allocation."""
+    import torch
+    from paper_1904_05347_amd import binding
+    t = torch.ones(4, 8)
+    for v in (t[:1].expand(4, 8), torch.ones(1, 1).expand(4, 1), t.as_strided((4, 8), (4, 1)), t.as_strided((2, 8), (7, 1))):
+        with pytest.raises(ValueError, match="overlap"):
+            binding._ld_2d(v, "a")
+    for v, ld in ((t, 8), (t[:, :5], 8), (t[:1].expand(1, 8), 8), (t[:, :1], 8), (torch.ones(0, 8), 8), (torch.ones(4, 0), 1),
+                  (t[1:2, 2:5], 8), (t.as_strided((1, 8), (0, 1)), 8)):
+        assert binding._ld_2d(v, "a") == ld

@@ -76,7 +76,9 @@ def test_native_calls_decline_and_raise_as_before(monkeypatch):
     bad = [
         lambda: pk.gemm(a.double(), a), lambda: pk.gemm(a.cpu(), a), lambda: pk.gemm(a, a[:4]),
         lambda: pk.gemm(a, a, beta=1.0), lambda: pk.gemm(a, a, beta=1e-50), lambda: pk.gemm(a, a, torch.ones(4, 8, device="cuda")),
-        lambda: pk.gemm(a.t()[:, :4], a), lambda: pk.gemm(a, a, a), lambda: pk.conv2d_fwd(x[0], w),
+        lambda: pk.gemm(a.t()[:, :4], a), lambda: pk.gemm(a, a, a),
+        lambda: pk.gemm(a[:1].expand(8, 8), a), lambda: pk.gemm(a, a.as_strided((8, 8), (4, 1)), trans_b=True),
+        lambda: pk.gemm(a, a, a[:1].expand(8, 8)), lambda: pk.conv2d_fwd(x[0], w),
         lambda: pk.conv2d_fwd(x, w[:, :, :3]), lambda: pk.conv2d_fwd(x, w, padding="WIDE"),
         lambda: pk.conv2d_fwd(x, w, stride=0), lambda: pk.conv2d_fwd(x, w, out=x),
         lambda: pk.conv2d_winograd(x, w, tile=3), lambda: pk.conv2d_winograd(x, torch.ones(5, 5, 4, 4, device="cuda")),
