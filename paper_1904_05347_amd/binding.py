@@ -125,7 +125,9 @@ def load():
 
 
 # The native marshalling (csrc/pk_torch.cpp) of the plain tensor calls, bound to
-# the loaded library's entry points at first use.
+# the loaded library's entry points at first use.  It only saves host time:
+# where it was not built, or was built for another torch, the Python code below
+# makes the same C-ABI calls.
 EXT_PATH = os.path.join(HERE, "_pk_torch.so")
 _NATIVE_ENTRIES = ("pk_sgemm_ws", "pk_sgemm_workspace_bytes_for", "pk_conv2d_fwd", "pk_conv2d_workspace_bytes_for",
                    "pk_conv2d_out_dims", "pk_conv2d_same_pads", "pk_conv2d_winograd_tile_fwd",
@@ -133,18 +135,38 @@ _NATIVE_ENTRIES = ("pk_sgemm_ws", "pk_sgemm_workspace_bytes_for", "pk_conv2d_fwd
 _native = None
 
 
+class _PythonOnly:
+    """Stands in for the native module: declines every call."""
+
+    @staticmethod
+    def gemm(*args):
+        return None
+
+    conv2d_fwd = conv2d_winograd = gemm
+
+
 def _load_native():
     global _native
-    lib = load()
-    if not os.path.exists(EXT_PATH):
-        raise PkLibraryMissing("_pk_torch.so is not built: run `python -m paper_1904_05347_amd.build`")
+    try:
+        lib = load()
+    except (PkLibraryMissing, OSError):
+        return _PythonOnly  # the Python code raises it again, after its checks of the arguments
     import importlib.machinery
     import importlib.util
-    import torch  # noqa: F401  (the module links against torch's libraries)
-    loader = importlib.machinery.ExtensionFileLoader("_pk_torch", EXT_PATH)
-    mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_pk_torch", loader))
-    loader.exec_module(mod)
-    mod.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_ENTRIES), _check)
+    mod = _PythonOnly
+    try:
+        import torch
+        loader = importlib.machinery.ExtensionFileLoader("_pk_torch", EXT_PATH)
+        ext = importlib.util.module_from_spec(importlib.util.spec_from_loader("_pk_torch", loader))
+        loader.exec_module(ext)
+        if ext.torch_version != torch.__version__:
+            raise ImportError("built for torch " + ext.torch_version)
+        ext.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_ENTRIES), _check)
+        mod = ext
+    except ImportError as e:
+        import warnings
+        warnings.warn("calls are marshalled in Python, which costs about 8 us each: %s (%s); "
+                      "run `python -m paper_1904_05347_amd.build`" % (EXT_PATH, e), RuntimeWarning, stacklevel=3)
     _native = mod
     return mod
 

@@ -2,7 +2,8 @@
 
 Each .hip source under csrc/ is compiled by hipcc in parallel, then linked into a
 shared library next to this file; csrc/pk_torch.cpp (host code, torch's C++
-headers) becomes the Python module ``_pk_torch`` beside it.  Run as ``python -m paper_1904_05347_amd.build``.
+headers) becomes the Python module ``_pk_torch`` beside it, which the package
+can do without.  Run as ``python -m paper_1904_05347_amd.build``.
 
 ``python -m paper_1904_05347_amd.build --sanitized`` builds a second copy,
 ``_build_san/libpk_san.so``, whose HOST code (argument checks, shape
@@ -78,6 +79,7 @@ def build_ext() -> str:
     tlib = os.path.join(troot, "lib")
     tmp = EXT + ".tmp%d" % os.getpid()
     cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+            '-DPK_TORCH_VERSION="%s"' % torch.__version__,
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi())]
            + ["-isystem" + d for d in (os.path.join(troot, "include"),
                                        os.path.join(troot, "include", "torch", "csrc", "api", "include"),
@@ -92,13 +94,25 @@ def build_ext() -> str:
     return EXT
 
 
+def try_build_ext():
+    """build_ext(), or None (and no module left from before) where this host has
+    no g++ or torch's headers do not compile: calls are then marshalled in Python."""
+    try:
+        return build_ext()
+    except (ImportError, OSError, RuntimeError) as e:
+        sys.stderr.write("%s not built, calls will be marshalled in Python: %s\n" % (EXT, e))
+        if os.path.exists(EXT):
+            os.remove(EXT)
+        return None
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(BUILD, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
-        ext = ex.submit(build_ext)
+        ext = ex.submit(try_build_ext)
         results = list(ex.map(_compile, srcs))
-        ext.result()
+        ext = ext.result()
     objs = [o for o, _ in results]
     with open(RESOURCE_LOG, "w") as fh:
         for _, remarks in results:
@@ -108,7 +122,7 @@ def build(verbose: bool = True) -> str:
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB)
     if verbose:
-        print("built", LIB, "and", EXT)
+        print("built", " and ".join(p for p in (LIB, ext) if p))
     return LIB
 
 

@@ -332,4 +332,10 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_pk_torch", "Native marshalling o
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__pk_torch(void) { return PyModule_Create(&kModule); }
+PyMODINIT_FUNC PyInit__pk_torch(void)
+{
+    PyObject *m = PyModule_Create(&kModule);
+    // the torch this was built for: binding.py takes no other
+    if (m && PyModule_AddStringConstant(m, "torch_version", PK_TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -444,3 +444,44 @@ def test_leading_dimension_of_overlapping_rows_is_refused():
     for v, ld in ((t, 8), (t[:, :5], 8), (t[:1].expand(1, 8), 8), (t[:, :1], 8), (torch.ones(0, 8), 8), (torch.ones(4, 0), 1),
                   (t[1:2, 2:5], 8), (t.as_strided((1, 8), (0, 1)), 8)):
         assert binding._ld_2d(v, "a") == ld
+
+
+def test_binding_without_the_native_module(pk, monkeypatch, tmp_path):
+    """Without the native marshalling module (not built, or not loadable) calls
+    go through the Python code; without the library too, an argument that is no
+    GPU tensor is still named first."""
+    import torch
+    from paper_1904_05347_amd import binding
+    a, x, w = torch.ones(4, 4), torch.ones(1, 5, 5, 4), torch.ones(3, 3, 4, 4)
+    bad = tmp_path / "bad.so"
+    bad.write_bytes(b"no module")
+
+    def calls():
+        for call in (lambda: pk.gemm(a, a), lambda: pk.conv2d_fwd(x, w), lambda: pk.conv2d_winograd(x, w)):
+            with pytest.raises(TypeError, match="float32 tensor on a HIP device"):
+                call()
+
+    for path in (str(tmp_path / "none.so"), str(bad)):
+        monkeypatch.setattr(binding, "EXT_PATH", path)
+        monkeypatch.setattr(binding, "_native", None)
+        with pytest.warns(RuntimeWarning, match="marshalled in Python"):
+            calls()
+    monkeypatch.setattr(binding, "_native", None)
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "LIB_PATH", str(tmp_path / "libnone.so"))
+    calls()
+
+
+def test_build_goes_on_without_the_native_module(monkeypatch, tmp_path, capsys):
+    from paper_1904_05347_amd import build
+    stale = tmp_path / "_pk_torch.so"
+    for error in (RuntimeError("g++ failed"), FileNotFoundError("g++"), ImportError("torch")):
+        stale.write_bytes(b"of another build")
+
+        def fails(error=error):
+            raise error
+
+        monkeypatch.setattr(build, "EXT", str(stale))
+        monkeypatch.setattr(build, "build_ext", fails)
+        assert build.try_build_ext() is None and not stale.exists()
+        assert "marshalled in Python" in capsys.readouterr().err
