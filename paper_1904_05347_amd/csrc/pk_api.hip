@@ -16,7 +16,6 @@
 
 #include <mutex>
 #include <string_view>
-#include <unordered_map>
 
 #include "../../include/pk.h"
 #include "pk_configs.hpp"
@@ -39,19 +38,32 @@ const Config *env_forced = nullptr;
 bool env_forced_bad = false;
 std::once_flag env_once;
 
-// The configuration of this name, or NULL (an index over the registry, built
-// at first use: a scan of its several hundred names costs a call 1-2 us).
+// The configuration of this name, or NULL: an open-addressed index over the
+// registry, built at first use (a scan of its several hundred names costs a
+// call 1-2 us) in static memory, so that no allocation can fail, that is throw,
+// under a C entry.  Names past what it holds at half load are scanned.
 const Config *find_config(const char *name)
 {
-    static const std::unordered_map<std::string_view, const Config *> index = [] {
-        std::unordered_map<std::string_view, const Config *> m;
+    constexpr int kSlots = 4096;
+    struct Index {
+        const Config *cfgs, *slot[kSlots] = {};
         int n = 0;
-        const Config *cfgs = pk::configs(&n);
-        for (int i = 0; i < n; ++i) m.emplace(cfgs[i].name, &cfgs[i]);
-        return m;
-    }();
-    const auto it = index.find(name);
-    return it == index.end() ? nullptr : it->second;
+        Index()
+        {
+            cfgs = pk::configs(&n);
+            for (int i = 0; i < n && i < kSlots / 2; ++i) {
+                size_t h = std::hash<std::string_view>()(cfgs[i].name) % kSlots;
+                while (slot[h]) h = (h + 1) % kSlots;
+                slot[h] = &cfgs[i];
+            }
+        }
+    };
+    static const Index index;
+    for (size_t h = std::hash<std::string_view>()(name) % kSlots; index.slot[h]; h = (h + 1) % kSlots)
+        if (strcmp(index.slot[h]->name, name) == 0) return index.slot[h];
+    for (int i = kSlots / 2; i < index.n; ++i)
+        if (strcmp(index.cfgs[i].name, name) == 0) return &index.cfgs[i];
+    return nullptr;
 }
 
 void read_env()

@@ -2,7 +2,33 @@
 // built by the CPU tests: the functions the calls use, not a copy of them.
 #include "../paper_1904_05347_amd/csrc/pk_api.hip"
 
+#include <new>
+
+// Allocations of this library's own code, refused on demand.
+static bool refuse_new = false;
+void *operator new(size_t n)
+{
+    if (refuse_new) throw std::bad_alloc();
+    return malloc(n);
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+
 extern "C" {
+
+// The status of a look-up by name while allocations are refused; -1: an exception.
+int shim_force_without_memory(const char *name)
+{
+    refuse_new = true;
+    int st = -1;
+    try {
+        st = pk_force_config(name);
+    } catch (...) {
+    }
+    refuse_new = false;
+    pk_force_config(nullptr);
+    return st;
+}
 
 // A configuration and its split: tile, K-block, groups of waves, stream-K,
 // split, predicted time (us, -1 outside the model).

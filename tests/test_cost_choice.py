@@ -58,7 +58,7 @@ def choice(pk, tmp_path_factory):
     subprocess.run([hipcc, "--offload-arch=gfx950", "-x", "hip", "-O1", "-std=c++20", "-shared", "-fPIC",
                     os.path.join(ROOT, "tests", "choice_shim.cpp"), "-o", out, "-L" + os.path.dirname(pk.binding.LIB_PATH),
                     "-l:" + os.path.basename(pk.binding.LIB_PATH),
-                    "-Wl,-rpath," + os.path.dirname(pk.binding.LIB_PATH)], check=True, capture_output=True)
+                    "-Wl,-Bsymbolic", "-Wl,-rpath," + os.path.dirname(pk.binding.LIB_PATH)], check=True, capture_output=True)
     lib = ctypes.CDLL(out)
     i64, sz, p = ctypes.c_int64, ctypes.c_size_t, ctypes.POINTER(_Pick)
     lib.shim_gemm.argtypes = [ctypes.c_int, ctypes.c_int, i64, i64, i64, ctypes.c_int, sz, p, p]
@@ -71,6 +71,16 @@ def choice(pk, tmp_path_factory):
 
     call.lib = lib
     return call
+
+
+def test_look_up_by_name_allocates_nothing(pk, choice):
+    """The first look-up builds its index without an allocation, whose failure
+    would leave the C entry as an exception; every name is found, others not."""
+    assert choice.lib.shim_force_without_memory(b"conv_64x64x32_w2x2_v44_dma2") == 0
+    assert choice.lib.shim_force_without_memory(b"conv_none") == 1
+    for c in pk.configs():
+        pk.force_config(c["name"])
+    pk.force_config(None)
 
 
 ALL_ROOM = (1 << 64) - 1
