@@ -1578,11 +1578,12 @@ int wino_fwd(int m, int m_pos, int ws_pos, const float *x, int64_t N, int64_t H,
 
     // One kernel where it is predicted faster than the three around a product
     // (a forced configuration names that product): 16-byte channel loads, an
-    // image addressed in 32-bit byte offsets, room for its filter.
-    if (!c && in4 && 4 * pixels * Cin < ((int64_t)1 << 31) && Cout <= 32 * 65535 &&
+    // image addressed in 32-bit byte offsets, room for its filter, a grid that
+    // holds it.
+    if (!c && in4 && 4 * pixels * Cin < ((int64_t)1 << 31) &&
         pk::wino_operand_floats(m, Cin, Cout) * sizeof(float) <= w.bytes) {
         const int form = pk::wino_form(m, w.T, Cin, Cout);
-        if (form >= 0) {
+        if (form >= 0 && pk::wino_fused_fits(m, form, w.T, Cout)) {
             if (pk::launch_wino_fused(m, form, x, f, U, y, H, W, Cin, Cout, pt, pl, w.TH, w.TW, w.T, Ho, Wo, out4, s) !=
                 hipSuccess)
                 return PK_ERR_LAUNCH;

@@ -84,7 +84,10 @@ hipError_t launch_wino_output(int m, const float *M, float *y, int64_t Ho, int64
 // (wino_operand_floats(m, Cin, Cout) floats), then the rest in one launch.  Cin
 // a multiple of 4, x and U 16-byte aligned, the image below 2 GiB; vec4: y
 // takes 16-byte stores.  form: the block of tiles x output channels.
+// wino_fused_fits: whether the launch's grid can hold T tiles (under 2^32
+// work-items, which small images with very wide padding pass) and Cout.
 size_t wino_operand_floats(int m, int64_t Cin, int64_t Cout);
+bool wino_fused_fits(int m, int form, int64_t T, int64_t Cout);
 hipError_t launch_wino_fused(int m, int form, const float *x, const float *f, float *U, float *y, int64_t H, int64_t W,
                              int64_t Cin, int64_t Cout, int64_t pt, int64_t pl, int64_t TH, int64_t TW, int64_t T,
                              int64_t Ho, int64_t Wo, bool vec4, hipStream_t stream);

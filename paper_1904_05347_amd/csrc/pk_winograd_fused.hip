@@ -377,6 +377,12 @@ size_t wino_operand_floats(int m, int64_t Cin, int64_t Cout)
     return (size_t)((m + 2) * (m + 2)) * (size_t)ks * 2 * (size_t)cb * 256;
 }
 
+bool wino_fused_fits(int m, int form, int64_t T, int64_t Cout)
+{
+    const int64_t threads = 64 * (m + 2) * (m == 4 && form == 1 ? 2 : 1), bc = form == 0 ? 32 : 64;
+    return (T + 31) / 32 * threads < ((int64_t)1 << 32) && (Cout + bc - 1) / bc <= 65535;
+}
+
 hipError_t launch_wino_fused(int m, int form, const float *x, const float *f, float *U, float *y, int64_t H, int64_t W,
                              int64_t Cin, int64_t Cout, int64_t pt, int64_t pl, int64_t TH, int64_t TW, int64_t T,
                              int64_t Ho, int64_t Wo, bool vec4, hipStream_t stream)

@@ -216,3 +216,15 @@ def test_workspace_query_for_the_operands_at_hand(pk, choice):
             assert plain >= max(need, aligned)
             differ += aligned < need
     assert differ > 50
+
+
+@pytest.mark.parametrize("m,form,threads,channels", [(2, 0, 256, 32), (2, 1, 256, 64), (4, 0, 384, 32), (4, 1, 768, 64)])
+def test_one_kernel_winograd_stays_within_a_grid(choice, m, form, threads, channels):
+    """32 tiles to a work-group of `threads`: a launch holds fewer than 2^32
+    work-items in x and at most 65535 blocks of channels in y."""
+    def fits(T, cout):
+        return choice.lib.shim_wino_fused_fits(m, form, ctypes.c_int64(T), ctypes.c_int64(cout))
+
+    most = ((1 << 32) - 1) // threads * 32
+    assert fits(1, 1) and fits(most, 65535 * channels)
+    assert not fits(most + 1, 1) and not fits(1, 65535 * channels + 1)
