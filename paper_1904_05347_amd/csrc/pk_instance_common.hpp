@@ -99,16 +99,15 @@ static hipError_t launch_gemm_streamk(const KernelArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool UA = false,
-          bool UB = false>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC>
 static int resident_dma_streamk(int beta)
 {
     static int per_cu[2] = {0, 0};  // the same on every MI355X
     const int b = beta ? 1 : 0;
     if (per_cu[b] == 0) {
-        auto kernel = gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false, UA, UB>;
+        auto kernel = gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false>;
         if constexpr (AMODE != A_CONV) {
-            if (b) kernel = gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true, UA, UB>;
+            if (b) kernel = gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true>;
         }
         int n = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 64 * WAVES_M * WAVES_N, 0) != hipSuccess ||
@@ -120,8 +119,7 @@ static int resident_dma_streamk(int beta)
 }
 
 // Stream-K launch of the direct-to-LDS contraction (as launch_gemm_streamk).
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool UA = false,
-          bool UB = false>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC>
 static hipError_t launch_gemm_dma_streamk(const KernelArgs &a, hipStream_t stream)
 {
     if (a.sk_groups < 1 || !a.sk_part || !a.sk_cnt || a.sk_nkb < 1) return hipErrorInvalidValue;
@@ -130,12 +128,12 @@ static hipError_t launch_gemm_dma_streamk(const KernelArgs &a, hipStream_t strea
     const dim3 grid((unsigned)a.sk_groups), block(64 * WAVES_M * WAVES_N);
     if constexpr (AMODE != A_CONV) {
         if (reads_c<AMODE>(a)) {
-            hipLaunchKernelGGL((gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true, UA, UB>),
+            hipLaunchKernelGGL((gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, true>),
                                grid, block, 0, stream, a);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false, UA, UB>), grid,
+    hipLaunchKernelGGL((gemm_dma_streamk_kernel<BM, BN, BK, WAVES_M, WAVES_N, STAGES, AMODE, TB, OCC, false>), grid,
                        block, 0, stream, a);
     return hipGetLastError();
 }

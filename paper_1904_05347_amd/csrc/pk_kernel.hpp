@@ -1923,15 +1923,14 @@ gemm_dma_ksplit_kernel(KernelArgs p)
 // there.  The epilogue's stores count on the same vector-memory counter as
 // the copies and retire in order, so a wait issued after them only waits
 // longer, never too little.
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool BETA,
-          bool UA = false, bool UB = false>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int AMODE, bool TB, int OCC, bool BETA>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(OCC, 8)))
 gemm_dma_streamk_kernel(KernelArgs p)
 {
     typedef GemmTile<BM, BN, BK, WAVES_M, WAVES_N, A_KCONTIG, false, 4, 4> G;  // MFMA and epilogue only
     constexpr int NT = G::NT, NW = NT / 64;
-    typedef typename DmaASel<AMODE, BM, BK, NW, UA>::T OpA;
-    typedef DmaOperand<BN, BK, NW, TB, UB> OpB;
+    typedef typename DmaASel<AMODE, BM, BK, NW, false>::T OpA;
+    typedef DmaOperand<BN, BK, NW, TB> OpB;
     constexpr int A_ST = OpA::FLOATS, B_ST = OpB::FLOATS;
     constexpr int LPB = OpA::L + OpB::L;
     static_assert(STAGES >= 2 && STAGES <= 4, "two to four LDS stages");
