@@ -49,13 +49,13 @@ def test_native_calls_equal_python_calls(monkeypatch):
     def rand(*shape):
         return torch.randn(shape, generator=g, device="cuda")
 
-    a, b, c0 = rand(70, 1030)[:, :1027], rand(45, 1027), rand(70, 45)
+    a, b, c0, d = rand(70, 1030)[:, :1027], rand(45, 1027), rand(70, 45), rand(70, 3)
     x, w = rand(2, 13, 11, 20), rand(3, 3, 20, 24)
     ws = torch.empty(1 << 20, device="cuda")
     calls = [
         lambda: pk.gemm(a, b, trans_b=True),
         lambda: pk.gemm(a, b, c0.clone(), alpha=2, beta=0.5, trans_b=True, workspace=ws),
-        lambda: pk.gemm(a, rand(70, 3), trans_a=True) * 0,
+        lambda: pk.gemm(a, d, trans_a=True),
         lambda: pk.conv2d_fwd(x, w),
         lambda: pk.conv2d_fwd(x, w, stride=2, padding="VALID"),
         lambda: pk.conv2d_fwd(x, w, stride=(2, 1), padding=(0, 1, 2, 1), out=torch.empty(2, 7, 11, 24, device="cuda"),

@@ -97,11 +97,46 @@ def test_winograd_every_product_config_forced(tile):
         out, used = _run(pk, x, f, (1, 1, 1, 1), force=cfg["name"], tile=tile)
         assert used == cfg["name"]
         _check_integers(tile, out, ref, sc, cfg["name"])
-        if cfg["vec_a"] == 1 and cfg["vec_b"] == 1:
+        if "_v11" in cfg["name"]:  # (the direct-to-LDS forms of any alignment report the width of their widest copy)
             out, used = _run(pk, xs, fs, (1, 1, 1, 1), force=cfg["name"], tile=tile)
             _check_integers(tile, out, ref_s, sc_s, cfg["name"])
         ran += 1
     assert ran >= 10
+
+
+# channel counts that no vector width divides (and one pair that two does),
+# and the direct-to-LDS form of any alignment that the batch of products runs on
+# with each tile size
+ODD_CHANNELS = [
+    ((1, 14, 13, 131, 97), "gemm_64x64x32_w2x2_nn_v11_dma2", "gemm_64x64x32_w2x2_nn_v11_dma2"),
+    ((2, 20, 22, 99, 149), "gemm_64x64x32_w2x2_nn_v11_dma2", "gemm_32x64x32_w1x2_k4_nn_v11_dma3"),
+    ((4, 56, 57, 150, 51), "gemm_128x64x32_w2x2_nn_v11_dma2", "gemm_64x64x16_w2x2_nn_v11_dma3"),
+    ((1, 9, 9, 101, 63), "gemm_32x64x32_w1x2_k4_nn_v11_dma3", "gemm_32x64x32_w1x2_k4_nn_v11_dma3"),
+]
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("geom,config2,config4", ODD_CHANNELS, ids=["x".join(map(str, o[0])) for o in ODD_CHANNELS])
+def test_winograd_odd_channels(geom, config2, config4, tile):
+    """Unforced products of odd channel counts: odd strides from one product of
+    the batch to the next, K-blocks that end inside a chunk, each product's own
+    last element, in a workspace filled with NaN."""
+    torch, pk = require_gpu()
+    N, H, W, Cin, Cout = geom
+    rng = np.random.default_rng(sum(geom) + tile)
+    for draw in (wl.uniform, wl.integers):
+        x = draw(rng, N * H * W * Cin).reshape(N, H, W, Cin)
+        f = draw(rng, 9 * Cin * Cout).reshape(3, 3, Cin, Cout)
+        ws = torch.full((pk.conv2d_winograd_workspace_bytes(N, H, W, Cin, Cout, 1, 1, 1, 1, tile) // 4,), float("nan"),
+                        dtype=torch.float32, device="cuda")
+        y = torch.full((N, H, W, Cout), float("nan"), dtype=torch.float32, device="cuda")
+        out = host(pk.conv2d_winograd(dev(x), dev(f), padding=(1, 1, 1, 1), out=y, workspace=ws, tile=tile))
+        assert pk.last_config_name() == (config2 if tile == 2 else config4)
+        ref, _ = oracle.conv2d(x, f, (1, 1), (1, 1, 1, 1))
+        if draw is wl.integers:
+            _check_integers(tile, out, ref, _scale(tile, x, f, (1, 1, 1, 1)), str(geom))
+        else:
+            assert_parity(out, ref, _scale(tile, x, f, (1, 1, 1, 1)), "F(%d) %s" % (tile, geom))
 
 
 def test_winograd_rejects_other_windows_and_workspace():
