@@ -802,16 +802,15 @@ size_t choice_bytes(const Choice &ch, int64_t M, int64_t N)
 }
 
 // The split of a chosen configuration: the thread's forced one, else the one
-// that came with the choice (0: by_rule), if ws_bytes hold it.
-int settle_splits(Choice *ch, int splits, int by_rule, int64_t M, int64_t N, size_t ws_bytes)
+// given, if ws_bytes hold it.
+int settle_splits(Choice *ch, int splits, int64_t M, int64_t N, size_t ws_bytes)
 {
     if (t_forced_splits > 0) {
         ch->splits = t_forced_splits;
         if (ch->splits > 1 && ch->c->bres) return PK_ERR_NOT_SUPPORTED;
         return splits_fit(ch->splits, M, N, ws_bytes) ? PK_OK : PK_ERR_WORKSPACE;
     }
-    ch->splits = splits > 0 ? splits : by_rule;
-    if (!splits_fit(ch->splits, M, N, ws_bytes)) ch->splits = 1;
+    ch->splits = splits_fit(splits, M, N, ws_bytes) ? splits : 1;
     return PK_OK;
 }
 
@@ -847,7 +846,8 @@ int gemm_choice(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, in
     }
     ch->c = c;
     ch->splits = 1;
-    return c->streamk ? PK_OK : settle_splits(ch, splits, gemm_splits(c, M, N, K), M, N, ws_bytes);
+    if (c->streamk) return PK_OK;
+    return settle_splits(ch, splits > 0 ? splits : gemm_splits(c, M, N, K), M, N, ws_bytes);
 }
 
 // A convolution's sizes: M = N*Ho*Wo outputs of K = KH*KW*Cin products each.
@@ -896,8 +896,8 @@ int conv_choice(const ConvDims &d, bool x16, bool f16, size_t ws_bytes, bool ws1
         if (c && !fits(c)) c = nullptr;
         if (c) splits = t.splits;
         if (!c && !d.gemm_path) {
-            for (const char *name : {"direct_8x32x64_k32_p", "direct_8x32x64_k32"}) {
-                const Config *k = find_config(name);
+            static const Config *const direct[] = {find_config("direct_8x32x64_k32_p"), find_config("direct_8x32x64_k32")};
+            for (const Config *k : direct) {
                 if (k && fits(k)) {
                     c = k;
                     break;
@@ -923,7 +923,7 @@ int conv_choice(const ConvDims &d, bool x16, bool f16, size_t ws_bytes, bool ws1
     ch->c = c;
     ch->splits = 1;
     if (c->streamk || c->kind == pk::KIND_DIRECT) return PK_OK;
-    return settle_splits(ch, splits, choose_splits(c, d.M, d.Cout, d.K), d.M, d.Cout, ws_bytes);
+    return settle_splits(ch, splits > 0 ? splits : choose_splits(c, d.M, d.Cout, d.K), d.M, d.Cout, ws_bytes);
 }
 
 void fill_common(KernelArgs &a, const Config *c, int64_t M, int64_t N, int64_t K, int splits)
