@@ -187,6 +187,10 @@ int cheapest(const CostFamily &f, int64_t M, int64_t N, int64_t K, size_t ws_byt
         if (!usable(i)) continue;
         const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         const int64_t nkb = (K + c.bk - 1) / c.bk;
+        // (stream-K was fitted where a tile has at most four contributors, whose
+        // partial tiles the last one adds one after the other: 3 x 8 x 8 x 864 ->
+        // 40, 7x7, on two tiles 298 us against 59)
+        if (c.streamk && 2 * tiles < kCostCUs) continue;
         for (int s : kCostSplits) {
             // (a split that leaves a work-group under two K-blocks, or more
             // work-groups than the chip holds anyway, was never the fastest)

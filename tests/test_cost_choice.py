@@ -140,6 +140,13 @@ def test_choice_has_no_longer_chain_than_the_rules(choice):
     assert streamk >= 50  # the stream-K rule's own regime is among them
 
 
+def test_choice_takes_stream_k_only_with_tiles_for_half_the_chip(choice):
+    """(a tile's last contributor adds the others' partial tiles in turn)"""
+    for c in [(192, 40, 42336, 1, 1, 1), (49, 192, 50176, 1, 1, 1)] + list(_convs(random.Random(14), 20000)):
+        _, pick = choice("shim_conv", *c, ALL_ROOM)
+        assert not pick.streamk or -(-c[0] // 128) * -(-c[1] // 128) >= 128, c
+
+
 def test_choice_at_less_workspace(choice):
     """A workspace of just what the choice asks for gives the same choice as a
     larger one; with any less, the choice is neither predicted slower nor longer
