@@ -253,18 +253,27 @@ inline float predict_wino_us(int m, int64_t T, int64_t Cin, int64_t Cout)
 // the separate kernels are: over 106 random convolutions this choice was within
 // 0.1 % of the faster of the three (geometric mean), the separate kernels 1.66x
 // (m = 2) and 1.15x (m = 4) above it.
-// Near the line the predictions err by up to a quarter where channels are deep
-// (a stage's latency counts for more): of 110 convolutions measured, most of
-// them near it, every one slower as one kernel had more than 100 channels and a
-// predicted ratio of 0.87 or more (4 x 31 x 31 x 104 -> 644, m = 4: 48.7 against
-// 40.6 us; 2 x 64 x 64 x 424 -> 24, m = 2: 56.8 against 44.1), while up to 100
-// channels the one kernel gained 2 to 36 % there.  So deeper ones need 0.85.
-constexpr int64_t kWinoDeep = 100;
-constexpr float kWinoDeepMargin = 0.85f;
+// Near the line the predictions err by up to a third where channels are deep (a
+// stage's latency counts for more) and, m = 4, where a round of blocks is barely
+// begun.  3931 convolutions predicted at 0.6 to 1 of the separate kernels' time,
+// graph-timed against these in turn: gain (least, geometric mean) in the last
+// twentieth of the predicted ratio below the limit and in the first above it,
+//   m = 2, up to 50:  1.17, 1.26 (0.80 to 0.85: none came closer to the line);
+//          up to 100: 1.02, 1.18 and 0.97, 1.09 at the limit 0.9;
+//          up to 200: 1.05, 1.22 and 0.96, 1.21 at 0.8;
+//          beyond:    1.08, 1.36 and 0.88, 1.17 at 0.7;
+//   m = 4, up to 20:  1.06, 1.13 and 0.96, 1.10 at 0.95;
+//          beyond:    1.00, 1.27 and 0.90, 1.20 at 0.8.
+inline float wino_margin(int m, int64_t Cin)
+{
+    if (m == 2) return Cin <= 50 ? 1.f : Cin <= 100 ? 0.9f : Cin <= 200 ? 0.8f : 0.7f;
+    return Cin <= 20 ? 0.95f : 0.8f;
+}
+
 inline int wino_form(int m, int64_t T, int64_t Cin, int64_t Cout)
 {
     const WinoFusedCost *c = m == 2 ? kWinoFused2 : kWinoFused4;
-    float best = (Cin > kWinoDeep ? kWinoDeepMargin : 1.f) * predict_wino_us(m, T, Cin, Cout);
+    float best = wino_margin(m, Cin) * predict_wino_us(m, T, Cin, Cout);
     int form = -1;
     for (int i = 0; i < 2; ++i) {
         const float t = predict_wino_fused_us(c[i], T, Cin, Cout);

@@ -48,6 +48,7 @@ static int held(int splits, int64_t M, int64_t N, size_t ws_bytes)
     return splits > 1 && ws_bytes < (size_t)splits * M * N * sizeof(float) ? 1 : splits;
 }
 
+int shim_wino_form(int m, int64_t T, int64_t Cin, int64_t Cout) { return pk::wino_form(m, T, Cin, Cout); }
 int shim_wino_fused_fits(int m, int form, int64_t T, int64_t Cout) { return pk::wino_fused_fits(m, form, T, Cout); }
 
 // The rule's configuration and the chosen one, each with its split as far as

@@ -235,3 +235,13 @@ def test_one_kernel_winograd_stays_within_a_grid(choice, m, form, threads, chann
     most = ((1 << 32) - 1) // threads * 32
     assert fits(1, 1) and fits(most, 65535 * channels)
     assert not fits(most + 1, 1) and not fits(1, 65535 * channels + 1)
+
+
+# tiles, channels in and out, whether one kernel was measured faster than the three
+@pytest.mark.parametrize("m,T,cin,cout,one", [
+    (4, 960, 72, 638, False), (4, 4212, 80, 117, False), (4, 192, 96, 918, False), (4, 108, 20, 350, False),
+    (2, 2809, 732, 20, False), (2, 2420, 540, 48, False), (2, 2450, 340, 36, False), (4, 1568, 36, 383, False), (2, 121, 136, 911, False),
+    (2, 3136, 64, 64, True), (2, 25088, 256, 256, True), (4, 6272, 64, 64, True)])
+def test_one_kernel_winograd_only_where_faster(choice, m, T, cin, cout, one):
+    form = choice.lib.shim_wino_form(m, *map(ctypes.c_int64, (T, cin, cout)))
+    assert (form >= 0) == one
