@@ -104,6 +104,39 @@ def test_conv_unaligned_configs(geom):
     assert ran >= 14
 
 
+# one element, a ragged last work-group, one column, rows aligned but not C's;
+# the largest result summed one element per work-item, and beyond it four
+# elements each: a last work-item of four, three, two and one, rows of one, two,
+# three and five
+@pytest.mark.parametrize("M,N", [(1, 1), (3, 1), (1, 3), (192, 23), (37, 31), (16, 24), (1 << 14, 16), (87382, 3),
+                                 (1031, 255), (262147, 1), (131073, 2), (262145, 1),
+                                 (65537, 4), (52430, 5), (517, 509)])
+@pytest.mark.parametrize("splits", [2, 9, 16])
+def test_splitk_sum_of_rows_of_any_length(M, N, splits):
+    torch, pk = require_gpu()
+    K = 16 * 32 if M * N < 1000 else 16 * 16
+    rng = np.random.default_rng(M * 7 + N + splits)
+    A, B, C = (wl.integers(rng, r * c).reshape(r, c) for r, c in ((M, K), (K, N), (M, N)))
+    ws = torch.full((splits * M * N,), float("nan"), dtype=torch.float32, device="cuda")
+    pk.force_config("gemm_64x64x16_w2x2_nn_v11_dma3")
+    pk.force_splits(splits)
+    try:
+        ref0, _ = oracle.sgemm("N", "N", M, N, K, 1.0, A, K, B, N, 0.0, None, N)
+        for beta, slack in ((0.0, 0), (0.5, 0), (0.0, 3), (0.5, 2)):
+            dC = _inside_nan(torch, C, slack)
+            if beta == 0.0:
+                dC.fill_(float("nan"))
+            pk.gemm(dev(A), dev(B), dC, beta=beta, workspace=ws)
+            ref = ref0 + beta * C.astype(np.float64)  # exact on these integers
+            assert np.array_equal(host(dC).astype(np.float64), ref), (beta, slack)
+            if slack and M > 1:  # what lies between the rows stays
+                gap = dC.as_strided((M - 1, slack), (N + slack, 1), dC.storage_offset() + N)
+                assert bool(torch.isnan(gap).all())
+    finally:
+        pk.force_config(None)
+        pk.force_splits(0)
+
+
 def test_conv_unaligned_infinities_stay_in_their_windows():
     """An infinity or NaN in the image reaches exactly the outputs whose window
     holds it."""
