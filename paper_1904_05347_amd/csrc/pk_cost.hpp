@@ -45,11 +45,12 @@ struct CostFamily {
     const TileCost *tiles;
 };
 
-// products whose operands allow 16-byte accesses
+// products whose operands allow 16-byte accesses (the 128 x 96 tile's m was
+// fitted to 1.583: 5 of 24 products that took it were 2-10 % slower than the rule's)
 constexpr TileCost kCostGemm44Tiles[] = {
     {"gemm_256x256x32_w2x4_%s_v44_o2_dma2", 256, 256, 32, 1, 1, 0, 0.563f, 7.158f, 6.92f},
     {"gemm_128x128x32_w2x4_%s_v44_o2_dma2", 128, 128, 32, 1, 2, 0, 0.741f, 1.959f, 2.89f},
-    {"gemm_128x96x32_w4x1_%s_v44_dma2", 128, 96, 32, 1, 2, 0, 0.156f, 1.583f, 3.49f},
+    {"gemm_128x96x32_w4x1_%s_v44_dma2", 128, 96, 32, 1, 2, 0, 0.156f, 1.680f, 3.49f},
     {"gemm_128x64x32_w2x2_%s_v44_dma2", 128, 64, 32, 1, 3, 0, 0.360f, 1.099f, 2.70f},
     {"gemm_128x32x32_w4x1_%s_v44_dma2", 128, 32, 32, 1, 4, 0, 0.489f, 0.668f, 2.10f},
     {"gemm_64x64x32_w2x2_%s_v44_dma2", 64, 64, 32, 1, 5, 0, 0.297f, 0.631f, 1.83f},

@@ -263,3 +263,9 @@ def test_large_tiles_need_a_reduction(choice, M, N, K):
     """256 x 256 tiles were measured up to 1.4 times slower there."""
     _, pick = choice("shim_gemm", 0, 0, M, N, K, 0, ALL_ROOM)
     assert pick.bm * pick.bn < 256 * 256
+
+
+@pytest.mark.parametrize("ta,tb,M,N,K", [(1, 1, 2624, 3344, 244), (1, 0, 544, 3816, 1826), (0, 0, 968, 2656, 632)])
+def test_gemm_choice_avoids_what_was_measured_slower(choice, ta, tb, M, N, K):
+    _, pick = choice("shim_gemm", ta, tb, M, N, K, 1, ALL_ROOM)
+    assert (pick.bm, pick.bn) != (128, 96)
