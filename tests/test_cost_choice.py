@@ -247,15 +247,17 @@ def test_one_kernel_winograd_only_where_faster(choice, m, T, cin, cout, one):
     assert (form >= 0) == one
 
 
-# n, h, w, cin, window, cout, stride; the tile and least split that were measured
-# slower than the rule's
+# n, h, w, cin, window, cout, stride; the tile with its groups and the least split
+# that were measured slower than the rule's
 @pytest.mark.parametrize("n,h,w,cin,k,cout,s,tile,splits", [
-    (25, 29, 29, 72, 3, 64, 1, (32, 64, 32), 1), (6, 20, 13, 32, 3, 704, 1, (32, 64, 32), 1),
-    (21, 10, 10, 28, 7, 128, 2, (32, 64, 32), 1), (14, 20, 31, 32, 5, 80, 2, (64, 64, 16), 12),
-    (4, 12, 12, 112, 3, 600, 1, (64, 64, 16), 8), (5, 10, 10, 108, 3, 912, 2, (64, 64, 16), 16)])
+    (9, 116, 116, 256, 3, 192, 2, (64, 64, 32, 4), 1), (8, 51, 51, 196, 5, 144, 1, (64, 64, 32, 4), 1),
+    (5, 109, 109, 136, 5, 56, 1, (64, 64, 32, 4), 1),
+    (25, 29, 29, 72, 3, 64, 1, (32, 64, 32, 1), 1), (6, 20, 13, 32, 3, 704, 1, (32, 64, 32, 1), 1),
+    (21, 10, 10, 28, 7, 128, 2, (32, 64, 32, 1), 1), (14, 20, 31, 32, 5, 80, 2, (64, 64, 16, 1), 12),
+    (4, 12, 12, 112, 3, 600, 1, (64, 64, 16, 1), 8), (5, 10, 10, 108, 3, 912, 2, (64, 64, 16, 1), 16)])
 def test_conv_choice_avoids_what_was_measured_slower(choice, n, h, w, cin, k, cout, s, tile, splits):
     _, pick = choice("shim_conv", n * -(-h // s) * -(-w // s), cout, k * k * cin, 1, 1, 1, ALL_ROOM)
-    assert (pick.bm, pick.bn, pick.bk) != tile or pick.splits < splits
+    assert (pick.bm, pick.bn, pick.bk, pick.kg) != tile or pick.splits < splits
 
 
 @pytest.mark.parametrize("M,N,K", [(15975, 857, 51), (29403, 971, 64), (93636, 459, 64), (15975, 857, 128)])
