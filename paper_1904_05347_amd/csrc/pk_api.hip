@@ -1480,17 +1480,20 @@ const Config *select_wino_gemm(int nbatch, int64_t T, int64_t Cout, int64_t Cin,
         c = find_config(rule);
     }
     // ... unless a tile is predicted at least 10 % faster over the whole batch
-    // (not 256 x 256 ones, beside whose products V and M stream through memory:
-    // 14 of 39 such choices were 2-11 % slower, on average 4 % faster)
+    // (not 256 x 256 ones, nor aligned 128 x 128 ones short of the rule's line:
+    // V and M stream through memory beside their products, which the prediction
+    // doesn't hold; 14 of 39 and 3 of 37 such choices were 2-13 % slower, on
+    // average 4 % faster)
     static const CostConfigs k44(pk::kCostGemm44, true), k11(pk::kCostGemm11, true);
     const pk::CostFamily &f = vec_ok ? pk::kCostGemm44 : pk::kCostGemm11;
     const CostConfigs &k = vec_ok ? k44 : k11;
     const int r = c ? cost_tile(f, c) : -1;
     const Config *best = c;
     float us = r < 0 ? 0.f : kCostMargin * pk::predict_us(f, f.tiles[r], T, Cout, Cin, 1, nbatch);
+    const int too_large = vec_ok ? 128 * 128 : 256 * 256;
     for (int i = 0; r >= 0 && i < f.n; ++i) {
         const float t = pk::predict_us(f, f.tiles[i], T, Cout, Cin, 1, nbatch);
-        if (k.c[0][i] && f.tiles[i].bm * f.tiles[i].bn < 256 * 256 && dma_fits(k.c[0][i], Cin, Cout) && t < us) {
+        if (k.c[0][i] && f.tiles[i].bm * f.tiles[i].bn < too_large && dma_fits(k.c[0][i], Cin, Cout) && t < us) {
             best = k.c[0][i];
             us = t;
         }

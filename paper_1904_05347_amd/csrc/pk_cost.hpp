@@ -197,8 +197,9 @@ int cheapest(const CostFamily &f, int64_t M, int64_t N, int64_t K, size_t ws_byt
         // 40, 7x7, on two tiles 298 us against 59)
         if (c.streamk && 2 * tiles < kCostCUs) continue;
         // (a 256 x 256 tile's epilogue and fill hide behind nothing when the
-        // reduction is four K-blocks or less: 15975 x 857 x 51 42 us against 31)
-        if (c.bm * c.bn >= 256 * 256 && K <= 128) continue;
+        // reduction is eight K-blocks or less: 15975 x 857 x 51 42 us against 31,
+        // 14336 x 900 x 135 63 against 54)
+        if (c.bm * c.bn >= 256 * 256 && K <= 256) continue;
         for (int s : kCostSplits) {
             // (a split that leaves a work-group under two K-blocks, or more
             // work-groups than the chip holds anyway, was never the fastest)

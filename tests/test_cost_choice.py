@@ -260,7 +260,7 @@ def test_conv_choice_avoids_what_was_measured_slower(choice, n, h, w, cin, k, co
     assert (pick.bm, pick.bn, pick.bk, pick.kg) != tile or pick.splits < splits
 
 
-@pytest.mark.parametrize("M,N,K", [(15975, 857, 51), (29403, 971, 64), (93636, 459, 64), (15975, 857, 128)])
+@pytest.mark.parametrize("M,N,K", [(15975, 857, 51), (29403, 971, 64), (93636, 459, 64), (15975, 857, 128), (14336, 900, 135)])
 def test_large_tiles_need_a_reduction(choice, M, N, K):
     """256 x 256 tiles were measured up to 1.4 times slower there."""
     _, pick = choice("shim_gemm", 0, 0, M, N, K, 0, ALL_ROOM)
