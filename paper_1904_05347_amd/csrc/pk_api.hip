@@ -446,9 +446,11 @@ constexpr float kCostMargin = 0.9f;
 // time among the usable ones whose partial sums fit in ws_bytes, or the rule's
 // configuration at its split.  A choice that asks for less workspace than the
 // rule's also has to beat what the rules run without one: `bare`, unsplit.
+// extra: microseconds that the prediction of the family's tiles leaves out.
 template <typename F>
 const Config *choose(const pk::CostFamily &f, const Config *const *cfgs, const Config *rule, const Config *bare,
-                     int64_t M, int64_t N, int64_t K, size_t ws_bytes, int rule_splits, F usable, int *splits)
+                     int64_t M, int64_t N, int64_t K, size_t ws_bytes, int rule_splits, F usable, int *splits,
+                     float extra = 0.f)
 {
     int s = 1;
     float us = 0.f;
@@ -457,7 +459,7 @@ const Config *choose(const pk::CostFamily &f, const Config *const *cfgs, const C
     const int i = pk::cheapest(f, M, N, K, ws_bytes, chain, usable, &s, &us);
     auto faster_than = [&](const Config *c, int split, float margin) {
         const int t = cost_tile(f, c);
-        return t < 0 || us <= margin * pk::predict_us(f, f.tiles[t], M, N, K, split);
+        return t < 0 || us + extra <= margin * pk::predict_us(f, f.tiles[t], M, N, K, split);
     };
     const bool less = i >= 0 && (s < rule_splits || (rule->streamk && !cfgs[i]->streamk));
     if (i < 0 || !faster_than(rule, rule_splits, kCostMargin) || (less && !faster_than(bare, 1, 1.f))) {
@@ -559,10 +561,14 @@ const Config *predict_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int6
     if (!rule || rule->bres) return rule;
     auto usable = [&](int t) { return k.c[l][t] && dma_fits(k.c[l][t], lda, ldb); };
     const int want = gemm_splits(rule, M, N, K);
-    const Config *c = choose(f, k.c[l], rule, rule, M, N, K, SIZE_MAX, want, usable, splits);
+    // (two k-contiguous operands that end inside a chunk: the last K-block of
+    // both is copied by single elements, which the rule's tile does not do; 24
+    // of 845 NT products that left it were 2-10 % slower, all of about 10 us)
+    const float tail = !vec_ok && !ta && tb && K % 4 != 0 ? 0.8f : 0.f;
+    const Config *c = choose(f, k.c[l], rule, rule, M, N, K, SIZE_MAX, want, usable, splits, tail);
     if (splits_fit(*splits, M, N, ws_bytes)) return c;
     return choose(f, k.c[l], rule, rule, M, N, K, ws_bytes, splits_fit(want, M, N, ws_bytes) ? want : 1, usable,
-                  splits);
+                  splits, tail);
 }
 
 const Config *select_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
