@@ -630,9 +630,9 @@ gemm_kernel(KernelArgs p)
 //   k-major: a chunk over the end of a row holds what follows in memory, in
 //     columns of C that are never stored; past the operand's last element the
 //     buffer's range, set to it, answers each element with zero.
-// Bound by the matrix cores as the aligned form: 4001 x 3999 x 4003 in 948-951
+// Bound by the matrix cores as the aligned form: 4001 x 3999 x 4003 in 950-953
 // us in every layout on 256 x 256 tiles (135 TFLOP/s; 4-byte loads through
-// registers on 64 x 64 tiles reach 53-62).
+// registers on 64 x 64 tiles 1399-1467 us, 87-92).
 template <int R, int BK, int NW, bool KROWS, bool UNAL = false>
 struct DmaOperand {
     static constexpr int CPR = KROWS ? BK / 4 : R / 4;  // 16-byte chunks per LDS row
@@ -828,8 +828,8 @@ struct DmaConvA {
 // 4-byte gather it replaces (64 x 64 x 16: a vector load, its bounds test and
 // an LDS write per element) a slot costs one add, the bounds test and the
 // copy.  Bound by the vector instructions beside the MFMAs: 20 x 19 x 26 x 189
-// -> 280, 7x7: 660 against 845 us (78 TFLOP/s); 8 x 57 x 43 x 50 -> 75, 3x3: 38
-// against 45 us.
+// -> 280, 7x7: 538 against 844 us (95 TFLOP/s on 128 x 96 tiles); 8 x 57 x 43 x
+// 50 -> 75, 3x3: 34.9 against 44.3 us (128 x 32).
 template <int BM, int BK, int NW>
 struct DmaConvA1 {
     typedef DmaOperand<BM, BK, NW, true> Layout;

@@ -6,7 +6,7 @@
 // its launch 2.9 us, but marshalled in Python (attribute reads, two ctypes
 // calls, the allocations) a call took 12.5 us of host time, and that was the
 // rate at which a program could issue small calls; marshalled here it takes
-// 4.7 us.
+// 4.1 or 5.0 us (one or the other for the life of a process).
 //
 // Each function answers None whenever a call is anything but the plain case
 // (a tensor subclass, an active torch mode, another type, device, layout or

@@ -22,11 +22,11 @@
 // 6.7 us for m = 4; the products alone 0.85, 1.71, 1.92 and 3.84).  m = 2: two
 // work-groups of four waves share a CU.  m = 4: six waves leave two SIMDs half
 // idle, so the wide form splits its channels over twelve.
-// Measured against the three kernels (whole call): 32 x 56 x 56 x 64 -> 64 102 ->
-// 53 us, 4 x 56 x 56 x 64 -> 64 28 -> 15 us, 32 x 56 x 56 x 256 -> 256 650 -> 475 us
-// (m = 2); 32 x 56 x 56 x 64 -> 64 66 -> 43 us (m = 4).  Deep channels on few
-// tiles stay with the three kernels: a work-group walks all of Cin (1 x 14 x 14 x
-// 512 -> 512: 34 against 61 us; m = 4 from about 128 channels on).
+// Measured against the three kernels (whole call, graph-timed): 32 x 56 x 56 x
+// 64 -> 64 97 -> 53 us, 4 x 56 x 56 x 64 -> 64 25.8 -> 13.6 us, 32 x 56 x 56 x 256
+// -> 256 650 -> 476 us (m = 2); 32 x 56 x 56 x 64 -> 64 60.5 -> 41.1 us (m = 4).
+// Deep channels on few tiles stay with the three kernels: a work-group walks all
+// of Cin (1 x 14 x 14 x 512 -> 512: 61 us here, 29 there).
 // Tried and dropped: two groups of waves splitting the channels (1-8 %, on few
 // tiles only), copies and fetches two stages ahead (none: not the latency of
 // memory), 64 tiles x 64 channels on eight waves (slower throughout).
