@@ -454,9 +454,10 @@ const Config *choose(const pk::CostFamily &f, const Config *const *cfgs, const C
 {
     int s = 1;
     float us = 0.f;
+    // the rule's chain, to the end of a K-block of 32 (its own may be 16 deep)
     const int64_t chain =
         pk::chain_of(rule->bm, rule->bn, rule->bk, rule->kgroups, rule->streamk != 0, M, N, K, rule_splits);
-    const int i = pk::cheapest(f, M, N, K, ws_bytes, chain, usable, &s, &us);
+    const int i = pk::cheapest(f, M, N, K, ws_bytes, (chain + 31) / 32 * 32, usable, &s, &us);
     auto faster_than = [&](const Config *c, int split, float margin) {
         const int t = cost_tile(f, c);
         return t < 0 || us + extra <= margin * pk::predict_us(f, f.tiles[t], M, N, K, split);

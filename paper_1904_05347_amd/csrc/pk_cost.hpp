@@ -20,7 +20,7 @@
 // in all, reproduced to 6-10 % (rms).  Taking the configuration and split of
 // the least predicted time costs 2-4 % over the best of all of them
 // (geometric mean per group of shapes; the limit on chains below adds its
-// 0.4 to 2.1 %); the rules that stood before cost
+// 0.3 to 1.4 %); the rules that stood before cost
 // 6-13 % on aligned products, 17-19 % on aligned convolutions, and the 4-byte
 // kernels that served unaligned operands 21-36 % and 37-80 %.  Graph-timed
 // against these rules over 8 000 random products and as many convolutions, the
@@ -163,10 +163,12 @@ inline float predict_us(const CostFamily &f, const TileCost &c, int64_t M, int64
 // one of kg groups of waves, or, stream-K, a work-group's share of all tiles'
 // K-blocks (two work-groups per CU hold them).  The rounding error of a result
 // grows with it (about 7e-7 of the result at 1777, 1.1e-6 at 4096, 2-norm), so
-// the choice takes no longer one than the configuration it replaces: over
-// 60 000 random sizes per family this limit costs 0.4 % (aligned) and 0.9 % of
-// the predicted time of products and 1.4 to 2.1 % of convolutions' (geometric
-// mean); without it 4 to 9 and 14 to 24 % of them had a longer chain.
+// the choice takes no longer one than the configuration it replaces, to the end
+// of a K-block of 32 (a rule's split in K-blocks of 16 may end in the middle of
+// one: 2672 products against 2688 on 32-deep tiles, half the time): over
+// 60 000 random sizes per family this limit costs 0.3 % (aligned) and 0.5 % of
+// the predicted time of products and 1.4 % of convolutions' (geometric mean);
+// without it 4 to 7 and 14 to 20 % of them had a longer chain.
 inline int64_t chain_of(int bm, int bn, int bk, int kg, bool streamk, int64_t M, int64_t N, int64_t K, int64_t s)
 {
     const int64_t nkb = (K + bk - 1) / bk;
