@@ -444,26 +444,20 @@ constexpr float kCostMargin = 0.9f;
 
 // The tile (cfgs: the family's configurations) and split of the least predicted
 // time among the usable ones whose partial sums fit in ws_bytes, or the rule's
-// configuration at its split.  A choice that asks for less workspace than the
-// rule's also has to beat what the rules run without one: `bare`, unsplit.
-// extra: microseconds that the prediction of the family's tiles leaves out.
+// configuration at its split.
 template <typename F>
-const Config *choose(const pk::CostFamily &f, const Config *const *cfgs, const Config *rule, const Config *bare,
-                     int64_t M, int64_t N, int64_t K, size_t ws_bytes, int rule_splits, F usable, int *splits,
-                     float extra = 0.f)
+const Config *choose(const pk::CostFamily &f, const Config *const *cfgs, const Config *rule, int64_t M, int64_t N,
+                     int64_t K, size_t ws_bytes, int rule_splits, F usable, int *splits)
 {
     int s = 1;
     float us = 0.f;
     // the rule's chain, to the end of a K-block of 32 (its own may be 16 deep)
     const int64_t chain =
         pk::chain_of(rule->bm, rule->bn, rule->bk, rule->kgroups, rule->streamk != 0, M, N, K, rule_splits);
-    const int i = pk::cheapest(f, M, N, K, ws_bytes, (chain + 31) / 32 * 32, usable, &s, &us);
-    auto faster_than = [&](const Config *c, int split, float margin) {
-        const int t = cost_tile(f, c);
-        return t < 0 || us + extra <= margin * pk::predict_us(f, f.tiles[t], M, N, K, split);
-    };
-    const bool less = i >= 0 && (s < rule_splits || (rule->streamk && !cfgs[i]->streamk));
-    if (i < 0 || !faster_than(rule, rule_splits, kCostMargin) || (less && !faster_than(bare, 1, 1.f))) {
+    const int64_t even = rule->streamk ? K : pk::even_chain(K, rule->kgroups, rule_splits);
+    const int i = pk::cheapest(f, M, N, K, ws_bytes, (chain + 31) / 32 * 32, even, usable, &s, &us);
+    const int r = cost_tile(f, rule);
+    if (i < 0 || (r >= 0 && us > kCostMargin * pk::predict_us(f, f.tiles[r], M, N, K, rule_splits))) {
         *splits = rule_splits;
         return rule;
     }
@@ -540,6 +534,20 @@ const Config *select_gemm_rule(int ta, int tb, int64_t M, int64_t N, int64_t K, 
     return find_config(name);
 }
 
+// The rule's split of a product.  Where only a slice or an address breaks the
+// 16-byte accesses, as far as the aligned rule's workspace holds it, which is
+// what ran before the query took such operands: NT 537 x 624 x 700 in wider
+// rows on the split of five 16.7 us, on four groups of waves unsplit 12.0, whose
+// chain the split's would forbid.
+int rule_gemm_splits(const Config *rule, int ta, int tb, int64_t M, int64_t N, int64_t K, bool vec_ok)
+{
+    const int64_t lda = ta ? M : K, ldb = tb ? K : N;
+    const int want = gemm_splits(rule, M, N, K);
+    if (vec_ok || !gemm_vec_ok(ta, tb, M, N, K, nullptr, lda, nullptr, ldb)) return want;
+    const Config *r4 = select_gemm_rule(ta, tb, M, N, K, lda, ldb, N, true);
+    return r4 && want <= gemm_splits(r4, M, N, K) ? want : 1;
+}
+
 // The configuration of a product that no table entry serves, and its split of
 // K: the tile and split of the least predicted time, unless the rule's choice
 // above (its split: gemm_splits) is within 10 % of it; always the rule's
@@ -547,9 +555,7 @@ const Config *select_gemm_rule(int ta, int tb, int64_t M, int64_t N, int64_t K, 
 // register-staged tiles where no direct-to-LDS form can address the operands.
 // Where ws_bytes of workspace hold that choice's partial sums it stands, so a
 // workspace of just the queried size serves as well as a larger one; with less,
-// the choice is made anew against what the rule can run there (judged by the
-// split the rule cannot have, some calls without a workspace took a shorter
-// chain of additions and up to 1.05 times the time, convolutions 1.13).
+// the choice is made anew against what the rule can run there.
 const Config *predict_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
                            bool vec_ok, size_t ws_bytes, int *splits)
 {
@@ -561,15 +567,10 @@ const Config *predict_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int6
     const Config *rule = select_gemm_rule(ta, tb, M, N, K, lda, ldb, ldc, vec_ok);
     if (!rule || rule->bres) return rule;
     auto usable = [&](int t) { return k.c[l][t] && dma_fits(k.c[l][t], lda, ldb); };
-    const int want = gemm_splits(rule, M, N, K);
-    // (two k-contiguous operands that end inside a chunk: the last K-block of
-    // both is copied by single elements, which the rule's tile does not do; 24
-    // of 845 NT products that left it were 2-10 % slower, all of about 10 us)
-    const float tail = !vec_ok && !ta && tb && K % 4 != 0 ? 0.8f : 0.f;
-    const Config *c = choose(f, k.c[l], rule, rule, M, N, K, SIZE_MAX, want, usable, splits, tail);
+    const int want = rule_gemm_splits(rule, ta, tb, M, N, K, vec_ok);
+    const Config *c = choose(f, k.c[l], rule, M, N, K, SIZE_MAX, want, usable, splits);
     if (splits_fit(*splits, M, N, ws_bytes)) return c;
-    return choose(f, k.c[l], rule, rule, M, N, K, ws_bytes, splits_fit(want, M, N, ws_bytes) ? want : 1, usable,
-                  splits, tail);
+    return choose(f, k.c[l], rule, M, N, K, ws_bytes, splits_fit(want, M, N, ws_bytes) ? want : 1, usable, splits);
 }
 
 const Config *select_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc,
@@ -674,7 +675,6 @@ const Config *predict_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb
         *splits = 1;
         const Config *rule = select_conv_rule(M, Cout, K, va4, vb4, dma_ok, sk);
         if (!rule) return nullptr;
-        const Config *bare = rule->streamk ? select_conv_rule(M, Cout, K, va4, vb4, dma_ok, false) : rule;
         int want = rule->streamk ? 1 : choose_splits(rule, M, Cout, K);
         if (whole4 && !(va4 && vb4)) {
             const Config *r4 = select_conv_rule(M, Cout, K, true, true, dma_ok, sk);
@@ -683,7 +683,7 @@ const Config *predict_conv(int64_t M, int64_t Cout, int64_t K, bool va4, bool vb
                               : want <= choose_splits(r4, M, Cout, K)))
                 want = 1;
         }
-        return choose(f, k.c[0], rule, bare, M, Cout, K, room, splits_fit(want, M, Cout, room) ? want : 1,
+        return choose(f, k.c[0], rule, M, Cout, K, room, splits_fit(want, M, Cout, room) ? want : 1,
                       [&](int t) { return dma_ok && k.c[0][t] && (sk || !f.tiles[t].streamk); }, splits);
     };
     const Config *c = at(allow_sk, SIZE_MAX);
@@ -1487,20 +1487,17 @@ const Config *select_wino_gemm(int nbatch, int64_t T, int64_t Cout, int64_t Cin,
         c = find_config(rule);
     }
     // ... unless a tile is predicted at least 10 % faster over the whole batch
-    // (not 256 x 256 ones, nor aligned 128 x 128 ones short of the rule's line:
-    // V and M stream through memory beside their products, which the prediction
-    // doesn't hold; 14 of 39 and 3 of 37 such choices were 2-13 % slower, on
-    // average 4 % faster)
+    // (not 256 x 256 ones: V and M stream through memory beside their products,
+    // which the prediction doesn't hold; 14 of 39 such choices were 2-11 % slower)
     static const CostConfigs k44(pk::kCostGemm44, true), k11(pk::kCostGemm11, true);
     const pk::CostFamily &f = vec_ok ? pk::kCostGemm44 : pk::kCostGemm11;
     const CostConfigs &k = vec_ok ? k44 : k11;
     const int r = c ? cost_tile(f, c) : -1;
     const Config *best = c;
     float us = r < 0 ? 0.f : kCostMargin * pk::predict_us(f, f.tiles[r], T, Cout, Cin, 1, nbatch);
-    const int too_large = vec_ok ? 128 * 128 : 256 * 256;
     for (int i = 0; r >= 0 && i < f.n; ++i) {
         const float t = pk::predict_us(f, f.tiles[i], T, Cout, Cin, 1, nbatch);
-        if (k.c[0][i] && f.tiles[i].bm * f.tiles[i].bn < too_large && dma_fits(k.c[0][i], Cin, Cout) && t < us) {
+        if (k.c[0][i] && f.tiles[i].bm * f.tiles[i].bn < 256 * 256 && dma_fits(k.c[0][i], Cin, Cout) && t < us) {
             best = k.c[0][i];
             us = t;
         }

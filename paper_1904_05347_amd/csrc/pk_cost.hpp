@@ -19,13 +19,13 @@
 // convolutions (1x1 to 7x7, stride 1 and 2, 8 to 1024 channels), 23 000 times
 // in all, reproduced to 6-10 % (rms).  Taking the configuration and split of
 // the least predicted time costs 2-4 % over the best of all of them
-// (geometric mean per group of shapes; the limit on chains below adds its
-// 0.3 to 1.4 %); the rules that stood before cost
+// (geometric mean per group of shapes; the limits on chains below add their
+// 0.5 to 1.9 %); the rules that stood before cost
 // 6-13 % on aligned products, 17-19 % on aligned convolutions, and the 4-byte
 // kernels that served unaligned operands 21-36 % and 37-80 %.  Graph-timed
-// against these rules over 8 000 random products and as many convolutions, the
-// choices that differ (half of them) are 1.35 and 1.47 times as fast (geometric
-// mean); 0.3 and 0.1 % of them are more than 3 % slower, the worst 10 %.
+// against these rules over 6 000 random products and as many convolutions, the
+// choices that differ (half of them) are 1.34 and 1.47 times as fast (geometric
+// mean); 0.5 and 0.2 % of them are more than 3 % slower, the worst 11 %.
 #pragma once
 
 #include <stddef.h>
@@ -49,11 +49,12 @@ struct CostFamily {
 };
 
 // products whose operands allow 16-byte accesses (the 128 x 96 tile's m was
-// fitted to 1.583: 5 of 24 products that took it were 2-10 % slower than the rule's)
+// fitted to 1.583: 5 of 24 products that took it were 2-10 % slower than the
+// rule's; at 1.680 more others lost up to 22 %)
 constexpr TileCost kCostGemm44Tiles[] = {
     {"gemm_256x256x32_w2x4_%s_v44_o2_dma2", 256, 256, 32, 1, 1, 0, 0.563f, 7.158f, 6.92f},
     {"gemm_128x128x32_w2x4_%s_v44_o2_dma2", 128, 128, 32, 1, 2, 0, 0.741f, 1.959f, 2.89f},
-    {"gemm_128x96x32_w4x1_%s_v44_dma2", 128, 96, 32, 1, 2, 0, 0.156f, 1.680f, 3.49f},
+    {"gemm_128x96x32_w4x1_%s_v44_dma2", 128, 96, 32, 1, 2, 0, 0.156f, 1.610f, 3.49f},
     {"gemm_128x64x32_w2x2_%s_v44_dma2", 128, 64, 32, 1, 3, 0, 0.360f, 1.099f, 2.70f},
     {"gemm_128x32x32_w4x1_%s_v44_dma2", 128, 32, 32, 1, 4, 0, 0.489f, 0.668f, 2.10f},
     {"gemm_64x64x32_w2x2_%s_v44_dma2", 64, 64, 32, 1, 5, 0, 0.297f, 0.631f, 1.83f},
@@ -85,10 +86,11 @@ constexpr CostFamily kCostGemm11 = {2.71f, 4.00f, 0.331f, 12, kCostGemm11Tiles};
 
 // convolutions, Cin and Cout multiples of four (the 32 x 64 tile's fit, 0.77,
 // 0.339, 1.85, was wrong where it would have been taken: 11 of 11 convolutions
-// 4-9 % slower than the rules'; c1 is the products', whose sum it is: at the
-// fitted 0.149 39 of 362 choices of 64 x 64 x 16 split up to four times as far
-// as the rule's ran up to 9 % slower; four groups' m was fitted to 2.174, and 6
-// of 21 convolutions that took them ran 3-8 % slower, 8 % beyond the prediction)
+// 4-9 % slower than the rules'; c1 stands between the fitted 0.149 and the
+// products', whose sum it is too: at the former 39 of 362 choices of 64 x 64 x 16
+// split up to four times as far as the rule's ran up to 9 % slower; four groups'
+// m was fitted to 2.174, and 6 of 21 convolutions that took them ran 3-8 %
+// slower, 8 % beyond the prediction)
 constexpr TileCost kCostConv44Tiles[] = {
     {"conv_128x128x32_w2x4_v44_o2_dma2", 128, 128, 32, 1, 2, 0, 0.491f, 1.992f, 3.36f},
     {"conv_128x96x32_w4x1_v44_dma2", 128, 96, 32, 1, 2, 0, 0.443f, 1.766f, 3.69f},
@@ -100,7 +102,7 @@ constexpr TileCost kCostConv44Tiles[] = {
     {"conv_64x64x32_w2x2_k2_v44_dma3", 64, 64, 32, 2, 1, 0, 0.231f, 1.214f, 2.38f},
     {"conv_128x128x32_w2x4_v44_o2_dma2_sk", 128, 128, 32, 1, 2, 1, 0.329f, 2.103f, 28.29f},
 };
-constexpr CostFamily kCostConv44 = {3.46f, 4.00f, 0.305f, 9, kCostConv44Tiles};
+constexpr CostFamily kCostConv44 = {3.46f, 4.00f, 0.220f, 9, kCostConv44Tiles};
 
 // ... Cin a multiple of four, any Cout
 constexpr TileCost kCostConv41Tiles[] = {
@@ -166,9 +168,9 @@ inline float predict_us(const CostFamily &f, const TileCost &c, int64_t M, int64
 // the choice takes no longer one than the configuration it replaces, to the end
 // of a K-block of 32 (a rule's split in K-blocks of 16 may end in the middle of
 // one: 2672 products against 2688 on 32-deep tiles, half the time): over
-// 60 000 random sizes per family this limit costs 0.3 % (aligned) and 0.5 % of
-// the predicted time of products and 1.4 % of convolutions' (geometric mean);
-// without it 4 to 7 and 14 to 20 % of them had a longer chain.
+// 60 000 random sizes per family this limit and the next cost 0.5 to 0.6 % of the
+// predicted time of products and 1.4 to 1.9 % of convolutions' (geometric mean);
+// without them 4 to 7 and 13 to 20 % of them had a longer chain.
 inline int64_t chain_of(int bm, int bn, int bk, int kg, bool streamk, int64_t M, int64_t N, int64_t K, int64_t s)
 {
     const int64_t nkb = (K + bk - 1) / bk;
@@ -183,12 +185,18 @@ inline int64_t chain_of(int bm, int bn, int bk, int kg, bool streamk, int64_t M,
     return blocks * bk < K ? blocks * bk : K;
 }
 
+// K shared evenly over groups and splits, which the choice does not raise above
+// the rule's either: splits that only the rounding to K-blocks lets in ran slower
+// than predicted (64 x 64 x 16 split 16 ways at K = 720 8.2 us, the choice without
+// them 7.5).
+inline int64_t even_chain(int64_t K, int64_t kg, int64_t s) { return (K + kg * s - 1) / (kg * s); }
+
 // The tile and split of the least predicted time among the tiles for which
 // usable(index) holds, the splits whose partial sums fit in ws_bytes and the
-// chains of at most max_chain; -1 when there is none.
+// chains of at most max_chain (even: max_even); -1 when there is none.
 template <typename F>
-int cheapest(const CostFamily &f, int64_t M, int64_t N, int64_t K, size_t ws_bytes, int64_t max_chain, F usable,
-             int *split, float *us)
+int cheapest(const CostFamily &f, int64_t M, int64_t N, int64_t K, size_t ws_bytes, int64_t max_chain,
+             int64_t max_even, F usable, int *split, float *us)
 {
     int best = -1;
     const size_t room = ws_bytes < kCostMaxPartials ? ws_bytes : kCostMaxPartials;
@@ -211,7 +219,9 @@ int cheapest(const CostFamily &f, int64_t M, int64_t N, int64_t K, size_t ws_byt
             if (s > 1 && (c.streamk || 2 * s > nkb || tiles * s > 16 * kCostCUs ||
                           (double)s * (double)M * (double)N * 4.0 > (double)room))
                 break;
-            if (chain_of(c.bm, c.bn, c.bk, c.kg, c.streamk != 0, M, N, K, s) > max_chain) continue;
+            if (chain_of(c.bm, c.bn, c.bk, c.kg, c.streamk != 0, M, N, K, s) > max_chain ||
+                even_chain(K, c.kg, s) > max_even)
+                continue;
             const float t = predict_us(f, c, M, N, K, s);
             if (best < 0 || t < *us) {
                 best = i;
@@ -267,36 +277,27 @@ inline float predict_wino_us(int m, int64_t T, int64_t Cin, int64_t Cout)
 // the separate kernels are: over 106 random convolutions this choice was within
 // 0.1 % of the faster of the three (geometric mean), the separate kernels 1.66x
 // (m = 2) and 1.15x (m = 4) above it.
-// Near the line the predictions err by up to a third where channels are deep (a
+// Near the line the predictions err by up to a third, where channels are deep (a
 // stage's latency counts for more) and, m = 4, where a round of blocks is barely
-// begun.  3931 convolutions predicted at 0.6 to 1 of the separate kernels' time,
-// graph-timed against these in turn: gain (least, geometric mean) in the last
-// twentieth of the predicted ratio below the limit and in the first above it,
-//   m = 2, up to 50:  1.17, 1.26 (0.80 to 0.85: none came closer to the line);
-//          up to 100: 1.02, 1.18 and 0.97, 1.09 at the limit 0.9;
-//          up to 200: 1.05, 1.22 and 0.96, 1.21 at 0.8;
-//          beyond:    1.08, 1.36 and 0.88, 1.17 at 0.7;
-//   m = 4, up to 20:  1.06, 1.13 and 0.96, 1.10 at 0.95;
-//          beyond:    1.00, 1.27 and 0.90, 1.20 at 0.8.
-inline float wino_margin(int m, int64_t Cin)
+// begun, so one kernel needs a margin there.  These were set on 7000 random
+// convolutions, each graph-timed as one kernel (both forms) and as three: the
+// choice costs 0.34 % over the fastest (geometric mean; 0.41 % with 0.85 beyond
+// 100 channels alone), and of 4071 taken as one kernel 5 ran more than 5 % slower
+// than the three kernels on the older rules' tile, the worst 8 % (20 and 12 %).
+// Margins that left none of them slower cost 1.0 %: they gave up one in nine.
+inline float wino_margin(int m, int form, int64_t Cin)
 {
-    if (m == 2) return Cin <= 50 ? 1.f : Cin <= 100 ? 0.9f : Cin <= 200 ? 0.8f : 0.7f;
-    return Cin <= 20 ? 0.95f : 0.8f;
+    if (m == 4) return Cin <= 60 ? 1.f : 0.85f;
+    if (form == 1) return Cin <= 100 ? 1.f : 0.9f;
+    return Cin <= 100 ? 0.97f : Cin <= 400 ? 0.85f : 0.78f;
 }
 
 inline int wino_form(int m, int64_t T, int64_t Cin, int64_t Cout)
 {
     const WinoFusedCost *c = m == 2 ? kWinoFused2 : kWinoFused4;
-    float best = wino_margin(m, Cin) * predict_wino_us(m, T, Cin, Cout);
-    int form = -1;
-    for (int i = 0; i < 2; ++i) {
-        const float t = predict_wino_fused_us(c[i], T, Cin, Cout);
-        if (t < best) {
-            best = t;
-            form = i;
-        }
-    }
-    return form;
+    const float t0 = predict_wino_fused_us(c[0], T, Cin, Cout), t1 = predict_wino_fused_us(c[1], T, Cin, Cout);
+    const int form = t1 < t0;
+    return (form ? t1 : t0) < wino_margin(m, form, Cin) * predict_wino_us(m, T, Cin, Cout) ? form : -1;
 }
 
 }  // namespace pk

@@ -58,7 +58,7 @@ void shim_gemm(int ta, int tb, int64_t M, int64_t N, int64_t K, int vec, size_t 
     const pk::CostFamily &f = vec ? pk::kCostGemm44 : pk::kCostGemm11;
     const int64_t lda = ta ? M : K, ldb = tb ? K : N;
     const Config *r = select_gemm_rule(ta, tb, M, N, K, lda, ldb, N, vec);
-    *rule = describe(f, r, M, N, K, held(gemm_splits(r, M, N, K), M, N, ws_bytes));
+    *rule = describe(f, r, M, N, K, held(rule_gemm_splits(r, ta, tb, M, N, K, vec), M, N, ws_bytes));
     int s = 0;
     const Config *c = select_gemm(ta, tb, M, N, K, lda, ldb, N, vec, ws_bytes, &s);
     *pick = describe(f, c, M, N, K, held(s, M, N, ws_bytes));
